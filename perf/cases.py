@@ -97,13 +97,14 @@ def _generator(seed):
 def _values(dist, n, dtype, g):
     if dist == "uniform":
         return torch.rand(n, generator=g, device="cuda", dtype=dtype)
+    if dist == "cauchy":  # tan(pi (u - 1/2)): heavy tails, every value finite
+        u = torch.rand(n, generator=g, device="cuda", dtype=dtype).clamp_(1e-9, 1 - 1e-7)
+        return u.sub_(0.5).mul_(math.pi).tan_()
     x = torch.randn(n, generator=g, device="cuda", dtype=dtype)
     if dist == "normal":
         return x
     if dist == "lognormal":
         return x.exp_()
-    if dist == "cauchy":  # the ratio of two independent normals
-        return x.div_(torch.randn(n, generator=g, device="cuda", dtype=dtype))
     if dist == "quantized":  # 1024 levels of N(0, 1)
         return x.add_(4.0).mul_(128.0).floor_().clamp_(0, 1023).add_(0.5).div_(128.0).sub_(4.0)
     raise ValueError(dist)
