@@ -622,12 +622,17 @@ int knn_mean_ex(cps_handle *h, const float *P_dev, const float *f_dev, const flo
     // sampled distances, brackets, counters, ordinate sums, kept distances and ordinates
     std::lock_guard<std::mutex> lk(h->mu);
     cps::KnnFilterBufs w;
-    cps::knn_filter_shape(n, nq, h->cu_count, &w.nseg, &w.seg);
+    bool screen;
+    cps::knn_filter_shape(n, dim, nq, k, h->cu_count, &w.nseg, &w.seg, &screen);
     const size_t off_ab = align_up((size_t)nq * 16384 * sizeof(float), 256);
     const size_t off_cnt = off_ab + align_up((size_t)nq * 2 * sizeof(float), 256);
-    const size_t off_fs = off_cnt + align_up((size_t)nq * 2 * sizeof(uint32_t), 256);
-    const size_t off_k = off_fs + align_up((size_t)nq * sizeof(double), 256);
-    const size_t bytes = off_k + (size_t)nq * cps::kKnnKeptCap * 2 * sizeof(float);
+    const size_t off_fs = off_cnt + align_up((size_t)nq * cps::kKnnCntStride * sizeof(uint32_t), 256);
+    const size_t off_ctr = off_fs + align_up((size_t)nq * sizeof(double), 256);
+    const size_t off_k = off_ctr + 256;
+    const size_t off_a = off_k + align_up((size_t)nq * cps::kKnnKeptCap * 2 * sizeof(float), 256);
+    const size_t off_b = off_a + (screen ? align_up((size_t)cps::knn_split_elems(n, dim) * 2, 256) : 0);
+    const size_t off_t = off_b + (screen ? align_up((size_t)nq * 64 * 2, 256) : 0);
+    const size_t bytes = off_t + (screen ? align_up((size_t)nq * sizeof(float), 256) : 0);
     int rc = ensure_buffer(h->lws, h->lws_bytes, bytes, s);
     if (rc) return rc;
     char *base = (char *)h->lws;
@@ -635,7 +640,11 @@ int knn_mean_ex(cps_handle *h, const float *P_dev, const float *f_dev, const flo
     w.ab = (float *)(base + off_ab);
     w.cnt = (uint32_t *)(base + off_cnt);
     w.fsum = (double *)(base + off_fs);
+    w.centre = (float *)(base + off_ctr);
     w.K = (float *)(base + off_k);
+    w.A = screen ? base + off_a : nullptr;
+    w.Bq = base + off_b;
+    w.Tq = (float *)(base + off_t);
     hipError_t e = cps::launch_knn_filtered(P_dev, f_dev, Q_dev, n, dim, nq, k, w, out_dev, s);
     return e == hipSuccess ? CPS_OK : hip_fail(e);
   }

@@ -173,15 +173,26 @@ hipError_t launch_lts_finish(const cps_result *sel, const double *ksum, int64_t 
 struct KnnFilterBufs {
   float *Ds;           // nq x S: distances of the sampled points (S <= 16384)
   float *ab;           // 2 nq: the sampled brackets
-  uint32_t *cnt;       // 2 nq: kept count (cursor), #(d <= a)
+  uint32_t *cnt;       // nq x kKnnCntStride: kept count (cursor), #(d <= a)
   double *fsum;        // nq: the ordinates' sum over d <= a
+  float *centre;       // 16: the screen's origin
+  void *A;             // the screen's split points (bfloat16, knn_split_elems), or null: the
+                       // plain filter
+  void *Bq;            // the split queries (64 bfloat16 each at most)
+  float *Tq;           // ... and their thresholds
   float *K;            // nq x kKnnCap x 2: kept distances and ordinates
   int64_t nseg, seg;   // the filter's segments and points per segment
 };
 // kept distances per query (the filtered form); 8128 keeps the select kernel under half a
 // CU's LDS (two workgroups per CU; at 8192 it was 208 bytes over and ran one)
 constexpr int64_t kKnnKeptCap = 8128;
-void knn_filter_shape(int64_t n, int64_t nq, int cu_count, int64_t *nseg, int64_t *seg);
+// A query's two counters have a 128-byte line of their own: device atomics on one line wait for
+// each other (with 1024 queries' cursors on 32 lines, taking the 460 000 places of 1024
+// queries x 2^20 points, k = 64, added ~107 us to a filter of 268 us)
+constexpr int64_t kKnnCntStride = 32;
+void knn_filter_shape(int64_t n, int32_t dim, int64_t nq, int64_t k, int cu_count, int64_t *nseg,
+                      int64_t *seg, bool *screen);
+int64_t knn_split_elems(int64_t n, int32_t dim);
 hipError_t launch_knn_filtered(const float *P, const float *f, const float *Q, int64_t n,
                                int32_t dim, int64_t nq, int64_t k, const KnnFilterBufs &w,
                                cps_knn *out, hipStream_t stream);

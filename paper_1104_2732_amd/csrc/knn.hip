@@ -235,14 +235,57 @@ __device__ __forceinline__ float knn_dist_reg(const float (&row)[D > 0 ? D : 16]
   return s;
 }
 
+// ---- the screen's constants and operands (see knn_screen_kernel)
+
+constexpr int kScrWaves = 4;
+constexpr int kScrBlock = kScrWaves * kWave;
+constexpr int kScrTile = 32;         // points and queries per tile
+constexpr int kScrK = 16;            // terms per matrix instruction
+constexpr int kScrList = 2 * kWave;  // pairs a wavefront's list holds
+constexpr float kScrNormMax = 1e37f;
+constexpr float kScrMargin = 0x1p-14f;
+constexpr int kScrQt = 4;            // query tiles per wavefront (one where there are few queries)
+constexpr int kScrPerCu = 4;         // workgroups per CU, all resident at once
+constexpr double kScrPart = 1.0 / 24.0;  // see knn_use_screen
+
+// The terms of the screen: slot s < 3 dim is coordinate s % dim of the products hi.hi (s / dim
+// = 0), hi.lo (1) and lo.hi (2), points first; the next two are the point's norm in two parts
+// times one; the slots up to a whole instruction are zero.
+struct ScreenSlot {
+  int j;
+  bool product, lo_p, lo_q;
+  int norm;  // 1, 2: the norm's parts
+};
+__host__ __device__ constexpr __forceinline__ int screen_steps(int dim) { return (3 * dim + 2 + kScrK - 1) / kScrK; }
+__device__ __forceinline__ ScreenSlot screen_slot(int s, int dim) {
+  const int g = s < dim ? 0 : (s < 2 * dim ? 1 : 2);
+  const bool pr = s < 3 * dim;
+  return {pr ? s - g * dim : 0, pr, g == 2, g == 1, !pr && s < 3 * dim + 2 ? s - 3 * dim + 1 : 0};
+}
+__device__ __forceinline__ __bf16 bf16_part(float v, bool lo) {
+  const __bf16 hi = (__bf16)v;
+  return lo ? (__bf16)(v - (float)hi) : hi;
+}
+using BF8 = __bf16 __attribute__((ext_vector_type(8)));
+
 // The distances of the sampled points (runs of kPropRun at sample_stride apart), one query
-// per lane, the points as scalar loads; one run per workgroup along x.
+// per lane, the points as scalar loads; one run per workgroup along x.  The first workgroup
+// also leaves the mean of 64 points spread over P in centre[0, dim) (a coordinate whose mean
+// is not an ordinary number: 0), which the screen takes as its origin; any origin gives the
+// same results.
 template <int D>
 __global__ __launch_bounds__(kKnnBlock) void knn_sample_kernel(
     const float *__restrict__ P, const float *__restrict__ Q, int64_t n, int32_t dim, int64_t nq,
-    float *__restrict__ Ds) {
+    float *__restrict__ Ds, float *__restrict__ centre) {
   constexpr int DM = D > 0 ? D : 16;
   const int dd = D > 0 ? D : dim;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kWave) {
+    const int64_t i = (int64_t)threadIdx.x * (n / kWave);
+    for (int j = 0; j < dd; ++j) {
+      const double s = wave_sum((double)P[i * dd + j]) / kWave;
+      if (threadIdx.x == 0) centre[j] = fabs(s) < 1e18 ? (float)s : 0.0f;
+    }
+  }
   const int64_t q = (int64_t)blockIdx.y * kKnnBlock + threadIdx.x;
   const bool live = q < nq;
   float qv[DM];
@@ -251,13 +294,23 @@ __global__ __launch_bounds__(kKnnBlock) void knn_sample_kernel(
   const int S = sample_size(n);
   const int64_t stride = sample_stride(n, S);
   const int run = blockIdx.x;
-  for (int r = 0; r < kPropRun; ++r) {
-    const int64_t i = (int64_t)run * stride + r;
-    float row[DM];
+  using F4 = float __attribute__((ext_vector_type(4)));
+  static_assert(kPropRun % 4 == 0, "whole vectors per run");
+  // (a lane's run goes out as 16-byte stores of one 64-byte line of its query's array: as
+  // sixteen single stores 1024 queries x 16384 samples took 58 us)
+  CPS_GLOBAL F4 *dst = (CPS_GLOBAL F4 *)(Ds + (live ? q : 0) * S + run * kPropRun);
 #pragma unroll
-    for (int j = 0; j < DM; ++j) row[j] = j < dd ? P[i * dd + j] : 0.0f;
-    const float d = knn_dist_reg<D>(row, qv, dim);
-    if (live) Ds[q * S + run * kPropRun + r] = d;
+  for (int r = 0; r < kPropRun; r += 4) {
+    F4 d;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int64_t i = (int64_t)run * stride + r + e;
+      float row[DM];
+#pragma unroll
+      for (int j = 0; j < DM; ++j) row[j] = j < dd ? P[i * dd + j] : 0.0f;
+      d[e] = knn_dist_reg<D>(row, qv, dim);
+    }
+    if (live) dst[r / 4] = d;
   }
 }
 
@@ -272,12 +325,16 @@ struct KnnBracketShared {
 // One workgroup per query: its sampled bracket to ab[2c], ab[2c+1] ((+inf, -inf) where there
 // is none: the filter then keeps nothing but NaN and the select recomputes), and the filter's
 // counters of c cleared.
+// With the screen (nm > 0), also the query's operands: -2 q' (exact scaling) in slot order and
+// the threshold (a query that is not screened: zero terms, and everything passes).
 __global__ __launch_bounds__(kKnnBlock) void knn_bracket_kernel(
-    const float *__restrict__ Ds, int64_t n, int64_t k, int64_t nq, float *__restrict__ ab,
-    uint32_t *__restrict__ cnt, double *__restrict__ fsum) {
+    const float *__restrict__ Ds, const float *__restrict__ Q, const float *__restrict__ centre,
+    int64_t n, int32_t dim, int64_t k, int64_t nq, int32_t nm, float *__restrict__ ab,
+    uint32_t *__restrict__ cnt, double *__restrict__ fsum, __bf16 *__restrict__ B,
+    float *__restrict__ T) {
   __shared__ KnnBracketShared sh;
   const int64_t c = blockIdx.x;
-  if (threadIdx.x < 2) cnt[threadIdx.x * nq + c] = 0u;
+  if (threadIdx.x < 2) cnt[c * kKnnCntStride + threadIdx.x] = 0u;
   if (threadIdx.x == 2) fsum[c] = 0.0;
   const int S = sample_size(n);
   const CPS_GLOBAL float *src = (const CPS_GLOBAL float *)Ds + c * S;
@@ -288,12 +345,256 @@ __global__ __launch_bounds__(kKnnBlock) void knn_bracket_kernel(
     ab[2 * c] = use ? a : __builtin_inff();
     ab[2 * c + 1] = use ? b : -__builtin_inff();
   }
+  if (nm > 0 && threadIdx.x < kWave) {
+    const int lane = threadIdx.x;
+    const float *Qr = Q + c * dim;
+    const float e = lane < dim ? Qr[lane < dim ? lane : 0] - centre[lane < dim ? lane : 0] : 0.0f;
+    const double n2 = wave_sum((double)e * (double)e);
+    const bool wild = !(n2 < (double)kScrNormMax);
+    if (lane < nm * kScrK) {
+      const ScreenSlot sl = screen_slot(lane, dim);
+      const float v = -2.0f * (Qr[sl.j] - centre[sl.j]);
+      B[c * nm * kScrK + lane] =
+          sl.norm ? (__bf16)1.0f : (sl.product && !wild ? bf16_part(v, sl.lo_q) : (__bf16)0.0f);
+    }
+    if (lane == 0) {
+      const double hi = use ? (double)b : -__builtin_inf();
+      const double v = hi * (1.0 + (dim + 8) * 0x1p-24) - n2 * (1.0 - (double)kScrMargin) + 1e-36;
+      T[c] = hi == -__builtin_inf() ? -__builtin_inff()
+                                    : (wild ? __builtin_inff() : (float)(v + fabs(v) * 0x1p-23));
+    }
+  }
 }
 
-// The filter: one query per lane, the points of segment blockIdx.x as scalar loads.  A
-// distance with a < d < b (or NaN) is kept with its ordinate at a place reserved on the
-// query's cursor (rare for small k), if below kKnnCap; d <= a is counted and its ordinate
-// summed (in point order; the segments' sums added atomically).
+// The filter on the matrix cores, for queries whose k nearest are a small part of the points.
+// Nearly every distance lies above b, and that can be seen without forming it: with a centre
+// c near the data, p' = fl(p - c) and q' = fl(q - c),
+//     d = |p'|^2 - 2 p'.q' + |q'|^2  up to the rounding of p', q' and of the sums,
+// and |p'|^2 - 2 p'.q' with every value split in two bfloat16 parts (hi.hi + hi.lo + lo.hi per
+// product and the norm's two, 3 dim + 2 terms added in float) is a matrix product.  A pair whose screen exceeds b - |q'|^2 by more than the margin below is above b for
+// certain; every other pair's distance is formed in float in the fixed order (knn_dist) and
+// tested as in knn_filter_kernel, so the kept distances, the counts and the sums are the same
+// bits: the screen only decides which pairs need not be formed.
+//
+// The margin, u = 2^-24, D = dim.  (1) An exact-order d below b has a true value below
+// b (1 + (D + 4) u) (D + 2 roundings, each relative, as every term is positive).  (2) p' and q'
+// are off by u |p'| and u |q'|, which moves the true distance by at most a factor 1 + u and
+// 2.01 u (|p'|^2 + |q'|^2) more.  (3) hi is off by 2^-9 and hi + lo by 2^-18 of the value, so the
+// terms left out of 2 p'.q' are below 3.1 * 2^-18 (|p'|^2 + |q'|^2).  (4) The at most 50 float
+// additions, in whatever order and however the matrix instruction aligns its terms (2^-22 of
+// the terms' sum each), are off by less than 2^-16 (2 |p'|^2 + |q'|^2), the norms by D u and
+// their parts by 2^-18.  Together below 2^-14 (|p'|^2 + |q'|^2) with room to spare: the norm is
+// lowered by 2^-14 of itself, so each point carries its own share, and the threshold is
+// b (1 + (D + 8) u) - |q'|^2 (1 - 2^-14) + 1e-36, formed in double and rounded up.  A point or
+// query whose norm is not below 1e37 (NaN, infinities) is not screened: all its distances are
+// formed.
+//
+// Why this shape.  On gfx950 the vector instructions of a SIMD wait while its matrix pipe
+// runs, so what counts is the sum of both.  A tile of 32 x 32 pairs takes 64 cycles of
+// matrix instructions for dim 5 to 10 (the same product in float: 256, as many as 8 vector FMAs
+// per pair), and its sixteen results per lane fold to their minimum and one compare;
+// forming every distance takes 16 x 28 vector instructions.  The split operands of the points
+// are laid out once per call (knn_split_kernel: one 16-byte load per lane and instruction),
+// a wavefront keeps QT tiles of 32 queries, and the wavefronts of a workgroup take other
+// queries of the same points, so that a point's line is read from the caches once.
+// 1024 queries x 2^20 points in 8 dimensions, k = 64: the plain filter 745 us, the screen
+// 106 us after the split's 20 us (the same screen with float matrix instructions and the
+// norms as start values took 235 us); the whole call 849 -> 232 us.
+// The points' operands: for every point the 16 nm terms in slot order (a lane of the screen
+// loads eight at once), the norm as |p'|^2 (1 - 2^-14); the points past n - 1 of the last tile
+// repeat it.  A workgroup takes kSplitRows points through LDS, so that both its loads and its
+// stores are whole lines.  A point that is not screened gets zero terms and a norm of -inf:
+// it passes for every query.
+// (The dimension is a template argument: places in the tile divide by it, and with a runtime
+// divisor the divisions took longer than the memory, 38 us against 20 us at 2^20 x 8.)
+constexpr int kSplitRows = 128;
+template <int dim>
+__global__ __launch_bounds__(kKnnBlock) void knn_split_kernel(const float *__restrict__ P,
+                                                              const float *__restrict__ centre,
+                                                              int64_t n, __bf16 *__restrict__ A) {
+  constexpr int nm = screen_steps(dim), ld = dim + 1;
+  __shared__ float sp[kSplitRows * ld];  // rows of dim + 1 words: a row per lane hits all banks
+  __shared__ float sn[kSplitRows];
+  const int tid = threadIdx.x;
+  const int64_t r0 = (int64_t)blockIdx.x * kSplitRows;
+  const int64_t rows = (n + kScrTile - 1) / kScrTile * kScrTile;
+  const int nr = (int)(rows - r0 < kSplitRows ? rows - r0 : kSplitRows);
+  for (int t = tid; t < nr * dim; t += kKnnBlock) {
+    const int r = t / dim, j = t - r * dim;
+    const int64_t i = r0 + r < n ? r0 + r : n - 1;
+    sp[r * ld + j] = P[i * dim + j] - centre[j];
+  }
+  __syncthreads();
+  if (tid < nr) {
+    float nx = 0.0f;
+    for (int j = 0; j < dim; ++j) nx = nx + sp[tid * ld + j] * sp[tid * ld + j];
+    sn[tid] = nx < kScrNormMax ? nx * (1.0f - kScrMargin) : -__builtin_inff();
+  }
+  __syncthreads();
+  constexpr int groups = 2 * nm;
+  for (int t = tid; t < nr * groups; t += kKnnBlock) {
+    const int r = t / groups, g = t - r * groups;
+    const float nr2 = sn[r];
+    const bool wild = nr2 < 0.0f;
+    BF8 out;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const ScreenSlot sl = screen_slot(8 * g + e, dim);
+      const float v = sl.norm ? nr2 : sp[r * ld + sl.j];
+      const bool on = wild ? sl.norm == 1 : sl.norm || sl.product;
+      out[e] = on ? bf16_part(v, sl.norm ? sl.norm == 2 : sl.lo_p) : (__bf16)0.0f;
+    }
+    *(BF8 *)(A + ((r0 + r) * groups + g) * 8) = out;
+  }
+}
+
+// NM matrix instructions per tile (16 terms each), QT query tiles per wavefront.  wq wavefronts
+// of the workgroup take other queries (wq QT 32 per workgroup), kScrWaves / wq other points.
+template <int NM, int QT>
+__global__ __launch_bounds__(kScrBlock, 4) void knn_screen_kernel(
+    const float *__restrict__ P, const float *__restrict__ f, const float *__restrict__ Q,
+    const float *__restrict__ ab, const __bf16 *__restrict__ Bq, const float *__restrict__ Tq,
+    const __bf16 *__restrict__ A, int64_t n, int32_t dim, int64_t nq, int32_t wq, int64_t seg,
+    float *__restrict__ K, uint32_t *__restrict__ cnt, double *__restrict__ fsum) {
+  using F16 = float __attribute__((ext_vector_type(16)));
+  constexpr int NQ = QT * kScrTile;      // queries per wavefront
+  __shared__ uint32_t list[kScrWaves][kScrList];
+  __shared__ float slo[kScrWaves][NQ], shi[kScrWaves][NQ];
+  __shared__ double sfb[kScrWaves][NQ];  // the ordinates' sum over d <= a, and their count
+  __shared__ uint32_t sbelow[kScrWaves][NQ];
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int col = lane % kScrTile, half = lane / kScrTile;
+  const int64_t q0 = ((int64_t)blockIdx.y * wq + wv % wq) * NQ;
+  for (int t = lane; t < NQ; t += kWave) {
+    const bool live = q0 + t < nq;
+    const int64_t q = live ? q0 + t : 0;
+    slo[wv][t] = live ? ab[2 * q] : __builtin_inff();
+    shi[wv][t] = live ? ab[2 * q + 1] : -__builtin_inff();
+    sfb[wv][t] = 0.0;
+    sbelow[wv][t] = 0u;
+  }
+  // the query operands and thresholds (a query past the last one: nothing passes)
+  BF8 B[QT][NM];
+  float T[QT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const int64_t q = q0 + t * kScrTile + col;
+    const int64_t qc = q < nq ? q : nq - 1;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) B[t][m] = ((const BF8 *)Bq)[qc * (2 * NM) + 2 * m + half];
+    const float v = Tq[qc];
+    T[t] = q < nq ? v : -__builtin_inff();
+  }
+  const int64_t rb = (int64_t)blockIdx.x * seg;
+  const int64_t re = rb + seg < n ? rb + seg : n;
+  // the exact distance and tests of one pair per lane: point rb + r, query ql of the wavefront
+  auto exact = [&](bool on, uint32_t r, int ql) {
+    const int64_t i = rb + r, q = q0 + ql;
+    if (!on || i >= re || q >= nq) return;
+    const float fi = f[i];
+    float d = 0.0f;  // (knn_dist's order)
+    for (int j0 = 0; j0 < dim; j0 += 4) {
+      float pv[4], qv[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = j0 + e < dim ? j0 + e : j0;
+        pv[e] = P[i * dim + j];
+        qv[e] = Q[q * dim + j];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float dif = pv[e] - qv[e];
+        const float sq = dif * dif;
+        if (j0 + e < dim) d = j0 + e == 0 ? sq : d + sq;
+      }
+    }
+    if (d <= slo[wv][ql]) {
+      atomicAdd(&sbelow[wv][ql], 1u);
+      atomicAdd(&sfb[wv][ql], (double)fi);
+    } else if (!(d >= shi[wv][ql])) {
+      const uint32_t at = atomicAdd(&cnt[q * kKnnCntStride], 1u);
+      if (at < (uint32_t)kKnnCap) {
+        K[2 * (q * kKnnCap + at)] = d;
+        K[2 * (q * kKnnCap + at) + 1] = fi;
+      }
+    }
+  };
+  uint32_t held = 0;  // pairs in the list (uniform)
+  auto drain = [&](uint32_t count) {  // the list's last `count` (<= 64) pairs
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t e = lane < count ? list[wv][held - count + lane] : 0u;
+    held -= count;
+    exact(lane < count, e / NQ, (int)(e % NQ));
+    __builtin_amdgcn_wave_barrier();
+  };
+  // this wavefront's tiles of the segment
+  const uint32_t tiles = (uint32_t)((re - rb + kScrTile - 1) / kScrTile);
+  const uint32_t step = kScrWaves / wq;
+  const BF8 *Ab = (const BF8 *)A + (rb + col) * (2 * NM) + half;
+  BF8 a[NM];
+  auto load = [&](uint32_t tile, BF8 (&av)[NM]) {
+#pragma unroll
+    for (int m = 0; m < NM; ++m) av[m] = Ab[(int64_t)tile * (kScrTile * 2 * NM) + 2 * m];
+  };
+  uint32_t tile = wv / wq;
+  if (tile < tiles) load(tile, a);
+  for (; tile < tiles; tile += step) {
+    BF8 an[NM];
+    load(tile + step < tiles ? tile + step : tile, an);
+    // (result i of a lane is point 8 (i / 4) + 4 half + i % 4 of the tile)
+    // the pairs that pass: bit i of tile t's sixteen for result i
+    uint32_t hit[(QT + 1) / 2] = {};
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      F16 R = {};
+#pragma unroll
+      for (int m = 0; m < NM; ++m)
+        R = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m], B[t][m], R, 0, 0, 0);
+      float mm = R[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mm = __builtin_fminf(mm, R[i]);
+      if (ballot(mm <= T[t]) != 0) {  // (a tile in three has a pair that passes, mostly one)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float mg = __builtin_fminf(
+              __builtin_fminf(__builtin_fminf(R[4 * g], R[4 * g + 1]), R[4 * g + 2]), R[4 * g + 3]);
+          if (ballot(mg <= T[t]) == 0) continue;
+          uint32_t w = 0;
+#pragma unroll
+          for (int j = 3; j >= 0; --j) w = 2 * w + (R[4 * g + j] <= T[t] ? 1u : 0u);
+          hit[t / 2] |= w << (16 * (t % 2) + 4 * g);
+        }
+      }
+    }
+    for (int h = 0; h < (QT + 1) / 2; ++h) {
+      uint32_t w = hit[h];
+      for (;;) {  // each lane's next pair, until none has one
+        const uint64_t mask = ballot(w != 0);
+        if (mask == 0) break;
+        if (w != 0) {
+          const uint32_t b = (uint32_t)__builtin_ctz(w);
+          const uint32_t i = b % 16, ql = (2 * h + b / 16) * kScrTile + col;
+          list[wv][held + lane_rank(mask)] =
+              (tile * kScrTile + 8 * (i / 4) + 4 * half + i % 4) * NQ + ql;
+          w &= w - 1;
+        }
+        held += popc(mask);
+        if (held >= (uint32_t)kWave) drain(kWave);
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < NM; ++m) a[m] = an[m];
+  }
+  if (held) drain(held);
+  __builtin_amdgcn_wave_barrier();
+  for (int t = lane; t < NQ; t += kWave)
+    if (q0 + t < nq && sbelow[wv][t]) {
+      atomicAdd(&cnt[(q0 + t) * kKnnCntStride + 1], sbelow[wv][t]);
+      atomicAdd(&fsum[q0 + t], sfb[wv][t]);
+    }
+}
+
 template <int D>
 __global__ __launch_bounds__(kKnnBlock) void knn_filter_kernel(
     const float *__restrict__ P, const float *__restrict__ f, const float *__restrict__ Q,
@@ -320,7 +621,7 @@ __global__ __launch_bounds__(kKnnBlock) void knn_filter_kernel(
     const float d = knn_dist_reg<D>(row, qv, dim);
     const bool le = d <= lo;
     if (live && !le && !(d >= hi)) {
-      const uint32_t at = atomicAdd(&cnt[q], 1u);
+      const uint32_t at = atomicAdd(&cnt[q * kKnnCntStride], 1u);
       if (at < (uint32_t)kKnnCap) {
         K[2 * (q * kKnnCap + at)] = d;
         K[2 * (q * kKnnCap + at) + 1] = fi;
@@ -332,7 +633,7 @@ __global__ __launch_bounds__(kKnnBlock) void knn_filter_kernel(
     }
   }
   if (live && below) {
-    atomicAdd(&cnt[nq + q], below);
+    atomicAdd(&cnt[q * kKnnCntStride + 1], below);
     atomicAdd(&fsum[q], fb);
   }
 }
@@ -369,7 +670,7 @@ __global__ __launch_bounds__(kKnnBlock) void knn_select_kernel(
   const int64_t c = blockIdx.x;
   const int tid = threadIdx.x;
   const int dd = D > 0 ? D : dim;
-  const int64_t len = cnt[c], below = cnt[nq + c];
+  const int64_t len = cnt[c * kKnnCntStride], below = cnt[c * kKnnCntStride + 1];
   const float lo = ab[2 * c], hi = ab[2 * c + 1];
   const bool holds = lo < hi && below < k && k <= below + len && len <= kKnnCap;
   if (tid < dd) sq[tid] = Q[c * dd + tid];
@@ -462,7 +763,54 @@ __global__ __launch_bounds__(kKnnBlock) void knn_select_kernel(
   }
 }
 
-void knn_filter_shape(int64_t n, int64_t nq, int cu_count, int64_t *nseg, int64_t *seg) {
+// Whether the screen serves a call: by the part of the points expected below the bracket's
+// upper end (rank k and four standard deviations of the sample, as sample_bracket_rule), since
+// a pair that passes costs more than in the plain filter.  Whole calls, screen against plain
+// filter: 1024 queries x 2^17 points x 8, 3.6 % of the points below the end 216 against 245 us,
+// 4.3 % 271 against 274, 6.6 % 326 against 300; 1024 x 40000 x 5, 4.3 % 147 against 245, 14 %
+// 224 against 268; the line is at the first one's crossing.
+static bool knn_use_screen(int64_t n, int64_t k) {
+  const double S = (double)sample_runs(n) * kPropRun, p = ((double)k - 0.5) / (double)n;
+  return p + 4.0 * sqrt(p * (1.0 - p) / S) + 2.0 / S <= kScrPart;
+}
+
+// The screen's shape: matrix instructions per tile, query tiles per wavefront, and wavefronts
+// of a workgroup that take other queries (as many as the queries fill).
+struct ScreenShape {
+  int nm, qt, wq;
+  int64_t groups;
+};
+static ScreenShape knn_screen_shape(int32_t dim, int64_t nq) {
+  ScreenShape s;
+  s.nm = screen_steps(dim);
+  s.qt = nq > 2 * kScrTile ? kScrQt : 1;
+  const int64_t waves = (nq + s.qt * kScrTile - 1) / (s.qt * kScrTile);
+  s.wq = waves > 2 ? 4 : (waves > 1 ? 2 : 1);
+  s.groups = (waves + s.wq - 1) / s.wq;
+  return s;
+}
+
+int64_t knn_split_elems(int64_t n, int32_t dim) {
+  const int64_t rows = (n + kScrTile - 1) / kScrTile * kScrTile;
+  return rows * screen_steps(dim) * kScrK;
+}
+
+void knn_filter_shape(int64_t n, int32_t dim, int64_t nq, int64_t k, int cu_count, int64_t *nseg,
+                      int64_t *seg, bool *screen) {
+  *screen = knn_use_screen(n, k);
+  if (*screen) {
+    // kScrPerCu workgroups per CU over (segments x groups of queries);
+    // segments of whole tiles, at most 2^24 points (a pair's place in its 32-bit list word)
+    const ScreenShape s = knn_screen_shape(dim, nq);
+    int64_t ns = (int64_t)cu_count * kScrPerCu / s.groups;
+    if (ns < 1) ns = 1;
+    const int64_t round = (int64_t)kScrTile * (kScrWaves / s.wq);
+    int64_t sl = ((n + ns - 1) / ns + round - 1) / round * round;
+    if (sl > ((int64_t)1 << 24)) sl = (int64_t)1 << 24;
+    *nseg = (n + sl - 1) / sl;
+    *seg = sl;
+    return;
+  }
   // about 4 x 8 workgroups per CU over (segments x groups of kKnnBlock queries), segments of
   // at least 256 points
   const int64_t groups = (nq + kKnnBlock - 1) / kKnnBlock;
@@ -476,23 +824,65 @@ void knn_filter_shape(int64_t n, int64_t nq, int cu_count, int64_t *nseg, int64_
   *seg = sl;
 }
 
+template <int D>
+static void launch_knn_split(const float *P, const float *centre, int64_t n, int32_t dim, __bf16 *A,
+                             hipStream_t stream) {
+  if constexpr (D > 1)
+    if (dim < D) return launch_knn_split<D - 1>(P, centre, n, dim, A, stream);
+  const int64_t rows = (n + kScrTile - 1) / kScrTile * kScrTile;
+  knn_split_kernel<D><<<dim3((unsigned)((rows + kSplitRows - 1) / kSplitRows)), dim3(kKnnBlock), 0,
+                        stream>>>(P, centre, n, A);
+}
+
+template <int NM>
+static void launch_knn_screen_nm(const float *P, const float *f, const float *Q, int64_t n,
+                                 int32_t dim, int64_t nq, const ScreenShape &s,
+                                 const KnnFilterBufs &w, hipStream_t stream) {
+  const dim3 grid((unsigned)w.nseg, (unsigned)s.groups);
+  const __bf16 *A = (const __bf16 *)w.A;
+  if (s.qt == kScrQt)
+    knn_screen_kernel<NM, kScrQt><<<grid, dim3(kScrBlock), 0, stream>>>(
+        P, f, Q, w.ab, (const __bf16 *)w.Bq, w.Tq, A, n, dim, nq, s.wq, w.seg, w.K, w.cnt, w.fsum);
+  else
+    knn_screen_kernel<NM, 1><<<grid, dim3(kScrBlock), 0, stream>>>(
+        P, f, Q, w.ab, (const __bf16 *)w.Bq, w.Tq, A, n, dim, nq, s.wq, w.seg, w.K, w.cnt, w.fsum);
+}
+
+static hipError_t launch_knn_screen(const float *P, const float *f, const float *Q, int64_t n,
+                                    int32_t dim, int64_t nq, const KnnFilterBufs &w,
+                                    hipStream_t stream) {
+  const ScreenShape s = knn_screen_shape(dim, nq);
+  launch_knn_split<16>(P, w.centre, n, dim, (__bf16 *)w.A, stream);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (s.nm == 1) launch_knn_screen_nm<1>(P, f, Q, n, dim, nq, s, w, stream);
+  else if (s.nm == 2) launch_knn_screen_nm<2>(P, f, Q, n, dim, nq, s, w, stream);
+  else if (s.nm == 3) launch_knn_screen_nm<3>(P, f, Q, n, dim, nq, s, w, stream);
+  else launch_knn_screen_nm<4>(P, f, Q, n, dim, nq, s, w, stream);
+  return hipGetLastError();
+}
+
 hipError_t launch_knn_filtered(const float *P, const float *f, const float *Q, int64_t n,
                                int32_t dim, int64_t nq, int64_t k, const KnnFilterBufs &w,
                                cps_knn *out, hipStream_t stream) {
   const int64_t groups = (nq + kKnnBlock - 1) / kKnnBlock;
   const dim3 sg((unsigned)sample_runs(n), (unsigned)groups);
   if (dim == 8)
-    knn_sample_kernel<8><<<sg, dim3(kKnnBlock), 0, stream>>>(P, Q, n, dim, nq, w.Ds);
+    knn_sample_kernel<8><<<sg, dim3(kKnnBlock), 0, stream>>>(P, Q, n, dim, nq, w.Ds, w.centre);
   else
-    knn_sample_kernel<0><<<sg, dim3(kKnnBlock), 0, stream>>>(P, Q, n, dim, nq, w.Ds);
+    knn_sample_kernel<0><<<sg, dim3(kKnnBlock), 0, stream>>>(P, Q, n, dim, nq, w.Ds, w.centre);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  knn_bracket_kernel<<<dim3((unsigned)nq), dim3(kKnnBlock), 0, stream>>>(w.Ds, n, k, nq, w.ab,
-                                                                        w.cnt, w.fsum);
+  knn_bracket_kernel<<<dim3((unsigned)nq), dim3(kKnnBlock), 0, stream>>>(
+      w.Ds, Q, w.centre, n, dim, k, nq, w.A ? knn_screen_shape(dim, nq).nm : 0, w.ab, w.cnt, w.fsum,
+      (__bf16 *)w.Bq, w.Tq);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 fg((unsigned)w.nseg, (unsigned)groups);
-  if (dim == 8)
+  if (w.A) {
+    e = launch_knn_screen(P, f, Q, n, dim, nq, w, stream);
+    if (e != hipSuccess) return e;
+  } else if (dim == 8)
     knn_filter_kernel<8><<<fg, dim3(kKnnBlock), 0, stream>>>(P, f, Q, w.ab, n, dim, nq, w.seg, w.K,
                                                               w.cnt, w.fsum);
   else
