@@ -72,7 +72,9 @@ enum cps_status {
  *             the low 32 bits); the bit-exact comparison key.
  * value:      the selected element widened to double.
  * less, equal, greater: #(x < value), #(x == value), #(x > value).
- * passes:     full reads of the input array (pass 0 included) the call made.
+ * passes:     full reads of the input array (pass 0 included) the call made.  A default call
+ *             reads it once, or twice when a second read comes from the caches (small arrays);
+ *             more when the sampled interval misses the rank.
  * status:     a cps_status value. */
 typedef struct cps_result {
   uint64_t value_bits;
@@ -168,7 +170,8 @@ typedef struct cps_options {
 
 #define CPS_STATS_MAX_PASSES 96
 
-/* Per-call trace written by select_kth_ex when stats_dev is not NULL (device memory).
+/* Per-call trace written by select_kth_ex when stats_dev is not NULL (device memory).  A traced
+ * call always runs the cutting plane's passes, also with default options.
  * passes:       full reads of the input (pass 0 included).
  * work_passes:  all reduction passes, including those over the split buffers.
  * kelley_steps, bisect_steps: how each trial point was chosen.

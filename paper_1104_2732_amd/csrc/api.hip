@@ -52,12 +52,14 @@ namespace {
 // partials, two split buffers (one region of seg_R elements per workgroup each) and the
 // gather buffer.
 struct SelectLayout {
-  size_t st, sync, gh, sd, si, z0, z1, zf, sm, total;
+  size_t st, sync, gh, qsync, qhist, qrec, qslot, qkept, qcnt, sd, si, z0, z1, zf, sm, zq, total;
   int64_t slot_stride, seg_R, zcap, smp_n;
 };
 
+// quick: with the one-read selection's parts (its counters and bins, which every call leaves
+// zero, before anything that moves with the size: inside the cleared first part).
 SelectLayout select_layout(int64_t seg_R, int grid, int64_t zcap, int gmax, size_t esize,
-                           int64_t smp_n = 0) {
+                           int64_t smp_n = 0, bool quick = false) {
   SelectLayout L;
   size_t off = 0;
   L.st = off;
@@ -67,6 +69,20 @@ SelectLayout select_layout(int64_t seg_R, int grid, int64_t zcap, int gmax, size
   L.gh = off;  // histogram counters, inside the cleared first part of fresh memory
   off = align_up(off + cps::kHistWords * sizeof(uint64_t), 256);
   L.slot_stride = gmax;
+  L.qsync = L.qhist = L.qrec = L.qslot = L.qkept = L.qcnt = off;
+  if (quick) {
+    off = align_up(off + sizeof(cps::SyncCtl), 256);
+    L.qhist = off;
+    off = align_up(off + (size_t)cps::kQuickCopies * cps::kHistMaxBins * sizeof(uint32_t), 256);
+    L.qrec = off;
+    off = align_up(off + sizeof(cps::QuickRec), 256);
+    L.qslot = off;
+    off = align_up(off + 4 * (size_t)gmax * sizeof(int64_t), 256);
+    L.qkept = off;
+    off = align_up(off + (size_t)gmax * (cps::kSelectBlock / cps::kWaveSize) * sizeof(uint32_t), 256);
+    L.qcnt = off;
+    off = align_up(off + (size_t)gmax * sizeof(uint32_t), 256);
+  }
   L.sd = off;
   off = align_up(off + 8 * (size_t)gmax * sizeof(double), 256);
   L.si = off;
@@ -83,6 +99,8 @@ SelectLayout select_layout(int64_t seg_R, int grid, int64_t zcap, int gmax, size
   L.smp_n = smp_n;
   L.sm = off;
   off = align_up(off + (size_t)smp_n * esize, 256);
+  L.zq = off;
+  if (quick) off = align_up(off + (size_t)gmax * cps::kQuickGather * esize, 256);
   L.total = off;
   return L;
 }
@@ -241,6 +259,24 @@ int resolve(cps_handle *h, int64_t n, int dtype, const cps_options *opt, Resolve
   return CPS_OK;
 }
 
+// Whether a call is the plain default one (no option that shapes the method's passes).
+bool default_method(const cps_options *opt) {
+  if (!opt) return true;
+  cps_options d;
+  cps_default_options(&d);
+  return opt->maxit == d.maxit && opt->final_threshold == d.final_threshold &&
+         opt->partition_fraction == d.partition_fraction && opt->grid_blocks == 0 &&
+         (opt->block_threads == 0 || opt->block_threads == cps::kSelectBlock) &&
+         opt->spin_limit == 0 && opt->use_bracket == 0 && opt->hist_bits == d.hist_bits &&
+         opt->count_first == d.count_first && opt->transform == 0 && opt->cooperative == 0;
+}
+
+// The one-read selection copies the likely interval's elements from this many bytes of input on;
+// smaller inputs are read again for the rank's bin, from the caches.  Whole calls, copied / read
+// again: 16 MiB float32 35 / 34 us, 32 MiB float64 40 / 42, 64 MiB float32 45 / 55, 128 MiB 56 /
+// 81, 1 GiB 231 / 392, 2 GiB float64 413 / 725.
+constexpr size_t kQuickCopyBytes = (size_t)1 << 26;
+
 // bracket_dev: a device-side proposal (a, b, use) read by pass 0, or null.
 template <typename T>
 int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_options *opt,
@@ -249,13 +285,25 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
   Resolved r;
   int rc = resolve(h, n, sizeof(T) == 4 ? CPS_F32 : CPS_F64, opt, r);
   if (rc) return rc;
+  // The plain default call without a trace: one workgroup for what its registers hold, else the
+  // filter that reads x once.  (A trace describes the cutting plane's passes, so a traced call
+  // runs them; ranks 1 and n are pass 0's extremes, already one read: 2^28 float32 198 us.)
+  // Median of normal data, this way / the general kernel: float32 2^8 7 / 22 us, 2^14 7 / 55, 2^16
+  // 22 / 59, 2^20 28 / 66, 2^24 45 / 122, 2^28 231 / 454; float64 2^15 18 / 97, 2^28 413 / 808.
+  const bool plain = stats == nullptr && bracket_dev == nullptr && default_method(opt);
+  if (plain && n <= cps::quick_small_max<T>()) {
+    const hipError_t e = cps::launch_quick_small<T>(x, n, k, out, stream);
+    return e == hipSuccess ? CPS_OK : hip_fail(e);
+  }
   const int per_cu = sizeof(T) == 4 ? h->max_blocks_f32 : h->max_blocks_f64;
+  const bool quick = plain && k > 1 && k < n && n <= cps::kQuickMaxN && r.grid <= 1024;
   const SelectLayout L = select_layout(r.seg_R, r.grid, r.cfg.zcap, h->cu_count * per_cu, sizeof(T),
-                                       spec_sample_elems(n, sizeof(T), r.cfg.spec_min_n));
+                                       spec_sample_elems(n, sizeof(T), r.cfg.spec_min_n), true);
   rc = ensure_workspace(h, L.total, stream);
   if (rc) return rc;
   char *base = (char *)h->ws;
   cps::SelectArgs<T> a;
+  a.quick = cps::QuickArgs<T>{};
   a.x = x;
   a.n = n;
   a.k = k;
@@ -284,7 +332,26 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
   a.ghist = (uint64_t *)(base + L.gh);
   a.smp = L.smp_n > 0 ? (T *)(base + L.sm) : nullptr;
   a.smp_n = L.smp_n;
-  hipError_t e = cps::launch_select<T>(a, r.grid, r.cooperative, stream);
+  hipError_t e;
+  if (quick) {
+    cps::QuickArgs<T> &q = a.quick;
+    q.x = x;
+    q.n = n;
+    q.k = k;
+    q.rec = (cps::QuickRec *)(base + L.qrec);
+    q.slot = (int64_t *)(base + L.qslot);
+    q.slot_stride = L.slot_stride;
+    q.hist = (uint32_t *)(base + L.qhist);
+    q.kept = (uint32_t *)(base + L.qkept);
+    q.z0 = a.z[0];
+    q.seg_R = L.seg_R;
+    q.zq = (T *)(base + L.zq);
+    q.zcnt = (uint32_t *)(base + L.qcnt);
+    q.sync = (cps::SyncCtl *)(base + L.qsync);
+    e = cps::launch_quick_filter<T>(q, (size_t)n * sizeof(T) >= kQuickCopyBytes, r.grid, stream);
+    if (e != hipSuccess) return hip_fail(e);
+  }
+  e = cps::launch_select<T>(a, r.grid, r.cooperative, stream);
   if (e != hipSuccess) return hip_fail(e);
   return CPS_OK;
 }
@@ -872,7 +939,7 @@ int cps_reserve(cps_handle *h, int64_t n, int dtype) {
   const int per_cu = dtype == CPS_F32 ? h->max_blocks_f32 : h->max_blocks_f64;
   const SelectLayout L =
       select_layout(r.seg_R, r.grid, r.cfg.zcap, h->cu_count * per_cu, dtype_size(dtype),
-                    spec_sample_elems(n, dtype_size(dtype), r.cfg.spec_min_n));
+                    spec_sample_elems(n, dtype_size(dtype), r.cfg.spec_min_n), true);
   return ensure_workspace(h, L.total, nullptr);
 }
 

@@ -51,7 +51,9 @@
 namespace cps {
 
 enum Phase : int32_t {
-  PH_PASS0 = 0, PH_EVAL = 1, PH_GATHER = 2, PH_FINAL = 3, PH_DONE = 4, PH_HIST = 5
+  PH_PASS0 = 0, PH_EVAL = 1, PH_GATHER = 2, PH_FINAL = 3, PH_DONE = 4, PH_HIST = 5,
+  PH_EQ = 6  // minimum and maximum of the bracket's elements (a narrowed bracket that may
+             // hold one repeated value)
 };
 
 // status values mirror enum cps_status in cpselect.h
@@ -700,6 +702,47 @@ CPS_HD inline HistGeom<uint64_t> split_part_geometry(const CpState &s, int part,
     return g;
   }
   return hist_geometry(a, b, c.dtype, c.hist_bits);
+}
+
+// The state of a selection whose filter (one read of the input) narrowed the rank to the
+// elements with keys in [klo, khi], `cnt` of them with `less` below, too many to gather: the
+// next pass looks whether they are one repeated value.  `kept` elements (a superset) are in
+// split buffer 0, or none (-1).  False when an end is infinite (no value lies beyond it).
+CPS_HD inline bool cp_quick_state(CpState &s, int64_t n, int64_t k, uint64_t klo, uint64_t khi,
+                                  int64_t less, int64_t cnt, int64_t kept, const CpConfig &c) {
+  // (the key between the negative numbers' and +0's is -0's, which no element has)
+  const double top = unkey_T(khi, c.dtype);
+  const double lo = unkey_T(klo, c.dtype), hi = top == 0.0 && __builtin_signbit(top) ? next_down(top, c.dtype) : top;
+  if (!(lo > -__builtin_inf() && hi < __builtin_inf())) return false;
+  s = CpState{};
+  s.n = n;
+  s.k = k;
+  s.passes = 1;
+  s.work_passes = 1;
+  s.elements_read = n;
+  s.elements_written = kept < 0 ? 0 : kept;
+  s.yL = next_down(lo, c.dtype);
+  s.yR = next_up(hi, c.dtype);
+  s.cL = less;
+  s.cR = less + cnt;
+  s.lo = s.fmin = lo;
+  s.hi = s.fmax = hi;
+  s.wbuf = kept < 0 ? -1 : 0;
+  s.wlen = kept < 0 ? n : kept;
+  s.narrowed = 1;
+  s.phase = PH_EQ;
+  return true;
+}
+
+// After that pass: mn and mx are the least and greatest element of the bracket.
+CPS_HD inline void cp_after_equal(CpState &s, double mn, double mx, const CpConfig &c) {
+  s.work_passes++;
+  if (s.wbuf < 0) s.passes++;
+  s.elements_read += s.wlen;
+  s.lo = mn;
+  s.hi = mx;
+  s.lo_data = s.hi_data = 1;
+  cp_plan(s, c);  // (one distinct value left: done)
 }
 
 // After the exact select of rank k - cL among the working set's elements inside the

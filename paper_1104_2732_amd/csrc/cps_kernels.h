@@ -56,6 +56,40 @@ struct SyncCtl {
   uint32_t grp[kMaxGroups][32];
 };
 
+// ---- the one-read selection (quick.hip)
+constexpr int kQuickCopies = 4;     // copies of the interval's bins (workgroup mod copies)
+constexpr int kQuickGather = 8192;  // elements of the rank's bin that are gathered and selected
+constexpr int64_t kQuickMaxN = ((int64_t)1 << 32) - 1;  // (32-bit bins and their sums)
+
+// What the filter found before it read x.
+struct QuickRec {
+  uint64_t ka, kb;  // the likely interval (closed ordered keys)
+  uint64_t ia, ib;  // ... without repeated ends, which are counted apart
+  int32_t nan;      // the sample holds NaN: nothing else was done
+  int32_t copied;   // the elements of [ia, ib] are in split buffer 0
+};
+
+// What the filter writes for the kernel after it.
+template <typename T> struct QuickArgs {
+  const T *x;
+  int64_t n, k;
+  QuickRec *rec;         // null: no filter ran
+  int64_t *slot;         // per workgroup, slot_stride apart: #(x < interval), the two ends'
+  int64_t slot_stride;   // repeated values, NaN
+  uint32_t *hist;        // kQuickCopies sets of the interval's bins (zero between calls)
+  uint32_t *kept;        // per wavefront: elements copied
+  T *z0;                 // split buffer 0: seg_R elements per wavefront
+  int64_t seg_R;
+  T *zq;                 // per workgroup kQuickGather elements: the gathered bin
+  uint32_t *zcnt;        // ... and how many
+  SyncCtl *sync;         // arrival counters of the gather (zero between calls)
+};
+template <typename T> int64_t quick_small_max();
+template <typename T>
+hipError_t launch_quick_small(const T *x, int64_t n, int64_t k, cps_result *out, hipStream_t stream);
+template <typename T>
+hipError_t launch_quick_filter(const QuickArgs<T> &a, bool copy, int grid, hipStream_t stream);
+
 template <typename T> struct SelectArgs {
   const T *x;
   int64_t n, k;
@@ -80,6 +114,7 @@ template <typename T> struct SelectArgs {
   T *smp;              // pass 0's sample for the likely interval: the first vector of every
                        // tile of x (smp_n elements), or null
   int64_t smp_n;
+  QuickArgs<T> quick;  // the filter that ran before this kernel (rec null: none)
 };
 
 // ---- batched selection

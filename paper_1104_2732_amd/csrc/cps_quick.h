@@ -1,0 +1,285 @@
+// Building blocks of the one-read selection (quick.hip and the first part of the general
+// kernel): what the filter leaves for the kernel after it, and exact selects and sample
+// quantiles over keys that one workgroup holds in registers.
+#pragma once
+
+#include "cps_device.h"
+#include "cps_kernels.h"
+#include "cps_passes.h"
+#include "cps_sample.h"
+
+namespace cps {
+
+// ------------------------------------------------------------------ scans and folds
+
+// Inclusive prefix sum over the wavefront: four row shifts, then two row broadcasts.
+template <int CTRL, int ROWS> __device__ inline uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ inline uint32_t wave_scan_u32(uint32_t v) {
+  v += dpp_or_zero<0x111, 0xF>(v);
+  v += dpp_or_zero<0x112, 0xF>(v);
+  v += dpp_or_zero<0x114, 0xF>(v);
+  v += dpp_or_zero<0x118, 0xF>(v);
+  v += dpp_or_zero<0x142, 0xA>(v);
+  v += dpp_or_zero<0x143, 0xC>(v);
+  return v;
+}
+
+// Exclusive prefix sum over the workgroup in thread order (wsum: a word per wavefront).
+template <int BLOCK> __device__ inline uint32_t block_scan_u32(uint32_t v, uint32_t *wsum) {
+  const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+  const uint32_t x = wave_scan_u32(v);
+  if (lane == kWave - 1) wsum[wv] = x;
+  __syncthreads();
+  uint32_t off = 0;
+#pragma unroll
+  for (int w = 0; w < BLOCK / kWave; ++w) off += w < wv ? wsum[w] : 0u;
+  __syncthreads();
+  return off + x - v;
+}
+
+__device__ inline uint32_t shfl_xor_key(uint32_t v, int o) { return (uint32_t)__shfl_xor((int)v, o); }
+__device__ inline uint64_t shfl_xor_key(uint64_t v, int o) {
+  return (uint64_t)__shfl_xor((unsigned long long)v, o);
+}
+
+template <int BLOCK> struct RegSelShared {
+  uint32_t wsum[BLOCK / kWave];
+  uint64_t kmin[BLOCK / kWave], kmax[BLOCK / kWave];
+  uint32_t flag[BLOCK / kWave];
+  uint32_t bin[2], below[2], inb[2];  // a pick's bin, the count below it and its own
+  uint32_t cursor, less, equal;
+  uint64_t key, list[kWave];
+};
+
+// Minimum and maximum of the workgroup's keys (a thread without one: mn = ~0, mx = 0), and
+// whether any thread's flag is set.
+template <int BLOCK, typename Key>
+__device__ inline bool block_key_range(Key &mn, Key &mx, bool flag, RegSelShared<BLOCK> &sh) {
+  const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    const Key a = shfl_xor_key(mn, o), b = shfl_xor_key(mx, o);
+    mn = a < mn ? a : mn;
+    mx = b > mx ? b : mx;
+  }
+  const bool any = ballot(flag) != 0;
+  if (lane == 0) {
+    sh.kmin[wv] = (uint64_t)mn;
+    sh.kmax[wv] = (uint64_t)mx;
+    sh.flag[wv] = any ? 1u : 0u;
+  }
+  __syncthreads();
+  uint32_t f = 0;
+#pragma unroll
+  for (int w = 0; w < BLOCK / kWave; ++w) {
+    const Key a = (Key)sh.kmin[w], b = (Key)sh.kmax[w];
+    mn = a < mn ? a : mn;
+    mx = b > mx ? b : mx;
+    f |= sh.flag[w];
+  }
+  return f != 0;
+}
+
+// The smallest shift that brings a key range into `bins` bins.
+__device__ inline int range_shift(uint64_t span, int bins_log2) {
+  const int bits = span == 0 ? 0 : 64 - __builtin_clzll(span);
+  return bits > bins_log2 ? bits - bins_log2 : 0;
+}
+
+// The bin that holds rank r (1-based) of `hist` (4 bins per thread, in thread order), left in
+// slot `s` of the shared picks.  Callers pass the scan of their four bins.
+template <int BLOCK>
+__device__ inline void pick4(const uint32_t (&h)[4], uint32_t cum, uint32_t r, int s,
+                             RegSelShared<BLOCK> &sh) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (cum < r && r <= cum + h[j]) {
+      sh.bin[s] = threadIdx.x * 4 + j;
+      sh.below[s] = cum;
+      sh.inb[s] = h[j];
+    }
+    cum += h[j];
+  }
+}
+
+template <typename Key> struct RegSel {
+  Key key;
+  uint32_t less, equal;
+};
+
+// The r-th smallest (1-based) of the workgroup's keys (cnt of them in [klo, khi], r <= cnt; an
+// empty place holds ~0, which no number has), with its counts: histograms of 4 BLOCK bins narrow
+// the key range to the bin of the rank until the range is one key or holds at most 64 keys,
+// which one wavefront ranks by comparing each with all.  `hist` is 4 BLOCK words of LDS.
+template <typename T, int BLOCK, int PER>
+__device__ inline RegSel<typename Traits<T>::Key> regs_select(
+    const typename Traits<T>::Key (&k)[PER], uint32_t r, uint32_t cnt,
+    typename Traits<T>::Key klo, typename Traits<T>::Key khi, uint32_t *hist,
+    RegSelShared<BLOCK> &sh) {
+  using Key = typename Traits<T>::Key;
+  constexpr int kBinsLog2 = BLOCK == 1024 ? 12 : (BLOCK == 512 ? 11 : 10);
+  static_assert((4 * BLOCK) == (1 << kBinsLog2), "four bins per thread");
+  const int tid = threadIdx.x, lane = tid % kWave;
+  uint32_t base = 0;
+  while (klo != khi && cnt > (uint32_t)kWave) {
+    const int shift = range_shift((uint64_t)(khi - klo), kBinsLog2);
+    *reinterpret_cast<uint4 *>(&hist[4 * tid]) = uint4{0u, 0u, 0u, 0u};
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const Key d = k[j] - klo;
+      if (d <= khi - klo) atomicAdd(&hist[(uint32_t)(d >> shift)], 1u);
+    }
+    __syncthreads();
+    const uint4 q = *reinterpret_cast<const uint4 *>(&hist[4 * tid]);
+    const uint32_t h[4] = {q.x, q.y, q.z, q.w};
+    const uint32_t cum = block_scan_u32<BLOCK>(h[0] + h[1] + h[2] + h[3], sh.wsum);
+    pick4<BLOCK>(h, cum, r, 0, sh);
+    __syncthreads();
+    base += sh.below[0];
+    r -= sh.below[0];
+    cnt = sh.inb[0];
+    const Key lo = klo + ((Key)sh.bin[0] << shift);
+    const Key hi = lo + (((Key)1 << shift) - 1);
+    khi = hi < khi && hi >= lo ? hi : khi;
+    klo = lo;
+  }
+  if (klo == khi) return {klo, base, cnt};
+  // at most 64 keys in [klo, khi]
+  __syncthreads();
+  if (tid == 0) sh.cursor = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    if (k[j] - klo <= khi - klo) {
+      const uint32_t at = atomicAdd(&sh.cursor, 1u);
+      if (at < (uint32_t)kWave) sh.list[at] = (uint64_t)k[j];
+    }
+  }
+  __syncthreads();
+  if (tid < kWave) {
+    const Key mine = lane < (int)cnt ? (Key)sh.list[lane] : (Key)~(Key)0;
+    uint32_t less = 0, eq = 0;
+    for (uint32_t i = 0; i < cnt; ++i) {
+      const Key o = (Key)sh.list[i];
+      less += o < mine ? 1u : 0u;
+      eq += o == mine ? 1u : 0u;
+    }
+    if (lane < (int)cnt && less < r && r <= less + eq) {
+      sh.key = (uint64_t)mine;
+      sh.less = less;
+      sh.equal = eq;
+    }
+  }
+  __syncthreads();
+  return {(Key)sh.key, base + sh.less, sh.equal};
+}
+
+// ------------------------------------------------------------------ the sample's ends
+
+template <typename Key> struct SampleEnds {
+  Key ka, kb;  // the likely interval, as closed keys
+  Key ia, ib;  // ... without an end that is one repeated value (its elements are counted apart)
+};
+
+// The likely interval of rank k of n values from S of their keys, PER per thread in registers
+// (S = BLOCK PER; no NaN): the bins of sample ranks floor(q - d) and ceil(q + d), q = S p, p = (k -
+// 1/2) / n, d = 4 sqrt(S p (1 - p)) + 2 (four binomial standard deviations), each end's bin
+// split again (2 BLOCK sub-bins) until it holds at most a sixteenth of the samples between the
+// ranks or is one key (a value that repeats).  An end whose rank falls outside the sample is
+// open: the key of -inf or +inf.  Every workgroup that calls it on the same sample gets the
+// same interval.
+template <typename T, int BLOCK, int PER>
+__device__ inline SampleEnds<typename Traits<T>::Key> sample_ends(
+    const typename Traits<T>::Key (&v)[PER], typename Traits<T>::Key klo,
+    typename Traits<T>::Key khi, int64_t n, int64_t k, uint32_t *hist, RegSelShared<BLOCK> &sh) {
+  using Key = typename Traits<T>::Key;
+  constexpr int kBinsLog2 = BLOCK == 1024 ? 12 : (BLOCK == 512 ? 11 : 10);
+  constexpr uint32_t S = BLOCK * PER;
+  const int tid = threadIdx.x;
+  const double Sd = (double)S, p = ((double)k - 0.5) / (double)n;
+  const double q = Sd * p, d = 4.0 * __builtin_sqrt(Sd * p * (1.0 - p)) + 2.0;
+  const double r0 = __builtin_floor(q - d), r1 = __builtin_ceil(q + d);
+  const bool open0 = r0 < 1.0, open1 = r1 > Sd;
+  const uint32_t rank0 = open0 ? 1u : (uint32_t)r0, rank1 = open1 ? S : (uint32_t)r1;
+  const uint32_t most = (rank1 - rank0 + 1) / 16 + 4;
+  int sh0 = range_shift((uint64_t)(khi - klo), kBinsLog2), sh1 = sh0;
+  *reinterpret_cast<uint4 *>(&hist[4 * tid]) = uint4{0u, 0u, 0u, 0u};
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PER; ++j) atomicAdd(&hist[(uint32_t)((v[j] - klo) >> sh0)], 1u);
+  __syncthreads();
+  {
+    const uint4 w = *reinterpret_cast<const uint4 *>(&hist[4 * tid]);
+    const uint32_t h[4] = {w.x, w.y, w.z, w.w};
+    const uint32_t cum = block_scan_u32<BLOCK>(h[0] + h[1] + h[2] + h[3], sh.wsum);
+    pick4<BLOCK>(h, cum, rank0, 0, sh);
+    pick4<BLOCK>(h, cum, rank1, 1, sh);
+  }
+  __syncthreads();
+  Key f0 = klo + ((Key)sh.bin[0] << sh0), f1 = klo + ((Key)sh.bin[1] << sh1);  // first keys
+  uint32_t t0 = rank0 - sh.below[0], t1 = rank1 - sh.below[1];  // ranks inside the bins
+  uint32_t in0 = sh.inb[0], in1 = sh.inb[1];
+  for (;;) {
+    const bool s0 = !open0 && sh0 > 0 && in0 > most, s1 = !open1 && sh1 > 0 && in1 > most;
+    if (!s0 && !s1) break;  // (uniform)
+    constexpr int kHalf = 2 * BLOCK;  // sub-bins per end, the upper end's after the lower's
+    const int n0 = sh0 > kBinsLog2 - 1 ? sh0 - (kBinsLog2 - 1) : 0;
+    const int n1 = sh1 > kBinsLog2 - 1 ? sh1 - (kBinsLog2 - 1) : 0;
+    __syncthreads();
+    *reinterpret_cast<uint4 *>(&hist[4 * tid]) = uint4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    const Key m0 = ((Key)1 << sh0) - 1, m1 = ((Key)1 << sh1) - 1;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const Key d0 = v[j] - f0, d1 = v[j] - f1;
+      if (s0 && d0 <= m0) atomicAdd(&hist[(uint32_t)(d0 >> n0)], 1u);
+      if (s1 && d1 <= m1) atomicAdd(&hist[kHalf + (uint32_t)(d1 >> n1)], 1u);
+    }
+    __syncthreads();
+    const uint4 w = *reinterpret_cast<const uint4 *>(&hist[4 * tid]);
+    const uint32_t h[4] = {w.x, w.y, w.z, w.w};
+    const uint32_t cum = block_scan_u32<BLOCK>(h[0] + h[1] + h[2] + h[3], sh.wsum);
+    // (the upper half follows the lower bin's samples in the scan, where they were counted)
+    if (s0 && tid < BLOCK / 2) pick4<BLOCK>(h, cum, t0, 0, sh);
+    if (s1 && tid >= BLOCK / 2) pick4<BLOCK>(h, cum, t1 + (s0 ? in0 : 0u), 1, sh);
+    __syncthreads();
+    if (s0) {
+      f0 += (Key)sh.bin[0] << n0;
+      t0 -= sh.below[0];
+      sh0 = n0;
+    }
+    if (s1) {
+      f1 += (Key)(sh.bin[1] - kHalf) << n1;
+      t1 -= sh.below[1] - (s0 ? in0 : 0u);
+      sh1 = n1;
+    }
+    if (s0) in0 = sh.inb[0];
+    if (s1) in1 = sh.inb[1];
+  }
+  const Key kneg = Traits<T>::key(-t_inf<T>()), kpos = Traits<T>::key(t_inf<T>());
+  SampleEnds<Key> e;
+  // (-0's own key is no element's: +0 compares equal to it and has the next key)
+  const Key hole = Traits<T>::key(T(0)) - 1;
+  e.ka = open0 ? kneg : f0;
+  if (e.ka == hole) ++e.ka;
+  const Key l1 = f1 + (((Key)1 << sh1) - 1);
+  e.kb = open1 || l1 > kpos || l1 < f1 ? kpos : l1;
+  if (e.kb == hole) --e.kb;
+  e.ia = e.ka;
+  e.ib = e.kb;
+  if (!open0 && sh0 == 0) {
+    ++e.ia;
+    if (e.ia == hole) ++e.ia;
+  }
+  if (!open1 && sh1 == 0 && e.kb != e.ka) {
+    --e.ib;
+    if (e.ib == hole) --e.ib;
+  }
+  __syncthreads();
+  return e;
+}
+
+}  // namespace cps

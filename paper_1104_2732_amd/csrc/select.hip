@@ -30,6 +30,7 @@
 #include "cps_device.h"
 #include "cps_kernels.h"
 #include "cps_passes.h"
+#include "cps_quick.h"
 
 namespace cps {
 
@@ -98,6 +99,7 @@ template <typename T, int BLOCK> struct Shared {
   uint32_t lcnt;  // elements a gather pass staged in LDS
   uint32_t rh[kHistWords];  // key histogram of a histogram pass, or of both parts of a split
   T ring[BLOCK / kWave][2][Stage<T>::kSlots];  // split staging, per wavefront and part
+  RegSelShared<BLOCK> rsel;  // quick_enter's scans and final select
   // The launch's arguments for the out-of-line update: a reference to the kernel's own
   // argument would make the compiler copy it to every lane's scratch memory at launch
   // (~280 bytes per lane, ~70 MB for a full grid).
@@ -1086,6 +1088,44 @@ __device__ __noinline__ void spec_interval(const T *smp, int64_t nsmp, const CpC
   __syncthreads();
 }
 
+// Minimum and maximum of the walk's elements in [lo, hi] (out of line: rare, and its registers
+// stay out of the streaming loops').
+template <typename T, int BLOCK, int U>
+__device__ __noinline__ void equal_walk(Walk<T> wk, T lo, T hi, T &mn, T &mx) {
+  constexpr int V = Traits<T>::kVec;
+  using Vec = typename Traits<T>::Vec;
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const Span<T> &sp = wk.sp;
+  T a = t_inf<T>(), b = -t_inf<T>();
+  auto one = [&](T v, bool ok) {
+    const bool in = ok & (v >= lo) & (v <= hi);
+    a = in ? tmin(a, v) : a;
+    b = in ? tmax(b, v) : b;
+  };
+  const int64_t step = wk.wave_mode ? (int64_t)kWave * U : (int64_t)BLOCK * U;
+  const int64_t first = wk.wave_mode ? 0 : (int64_t)blockIdx.x * step;
+  const int64_t stride = wk.wave_mode ? step : (int64_t)gridDim.x * step;
+  const int me = wk.wave_mode ? lane : tid, per = wk.wave_mode ? kWave : BLOCK;
+  for (int64_t base = first; base < sp.nvec; base += stride) {
+    Vec raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t vi = base + (int64_t)u * per + me;
+      raw[u] = sp.V[vi < sp.nvec ? vi : 0];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < V; ++j) one(raw[u][j], base + (int64_t)u * per + me < sp.nvec);
+  }
+  if (sp.nedge > 0 && wk.edge_owner && (wk.wave_mode || tid < kWave)) {
+    const bool have = lane < sp.nedge;
+    one(have ? sp.W[edge_index(sp, lane)] : T(0), have);
+  }
+  mn = a;
+  mx = b;
+}
+
 // Workgroup partials each lane of the folding wavefront loads at once.
 constexpr int kFold = 4;
 
@@ -1218,6 +1258,18 @@ __device__ inline void run_pass(const SelectArgs<T> &a, Shared<T, BLOCK> &sh, in
   acc.succ = t_inf<T>();
   acc.L = acc.G = 0;
   int64_t written = 0;
+  if (s.phase == PH_EQ) {
+    T mn, mx;
+    equal_walk<T, BLOCK, SU>(wk, (T)s.lo, (T)s.hi, mn, mx);
+    dv[0] = (double)mn;
+    dv[1] = (double)mx;
+    dop[0] = 1;
+    dop[1] = 2;
+    block_reduce<BLOCK, 2, 0>(dv, dop, iv, false, sh.d, sh.i);
+    dv[2] = dv[3] = dv[4] = dv[5] = dv[6] = dv[7] = 0.0;
+    iv[0] = iv[1] = iv[2] = iv[3] = iv[4] = iv[5] = iv[6] = iv[7] = 0;
+    return;
+  }
   if (s.phase == PH_HIST) {
     const HistGeom<uint64_t> g = hist_geometry(s.lo, s.hi, a.cfg.dtype, a.cfg.hist_bits);
     for (int b = tid; b < g.nbins; b += BLOCK) sh.rh[b] = 0u;
@@ -1507,6 +1559,18 @@ __device__ __noinline__ void last_update(const SelectArgs<T> &a, Shared<T, BLOCK
     if (a.cfg.spec_min_n > 0 && a.n >= a.cfg.spec_min_n && a.seg_R > 0 && a.smp &&
         sh.st.phase == PH_EVAL && sh.st.counted && sh.st.wbuf < 0)
       spec_interval<T, BLOCK>(a.smp, a.smp_n, a.cfg, sh);
+  } else if (phase == PH_EQ) {
+    if (tid < kWave) {
+      rd[0] = __builtin_inf();
+      rd[1] = -__builtin_inf();
+      for (int b = tid; b < G; b += kWave) {
+        rd[0] = fmin(rd[0], a.sd[0 * stride + b]);
+        rd[1] = fmax(rd[1], a.sd[1 * stride + b]);
+      }
+      rd[0] = wave_min(rd[0]);
+      rd[1] = wave_max(rd[1]);
+    }
+    if (tid == 0) cp_after_equal(sh.st, rd[0], rd[1], a.cfg);
   } else if (phase == PH_HIST) {
     const CpState &s0 = sh.st;
     const HistGeom<uint64_t> g = hist_geometry(s0.lo, s0.hi, a.cfg.dtype, a.cfg.hist_bits);
@@ -1706,6 +1770,221 @@ __device__ __noinline__ void last_update(const SelectArgs<T> &a, Shared<T, BLOCK
   }
 }
 
+// The elements of this workgroup with keys in [klo, klo + span], appended to LDS `lbuf` (the
+// rank's bin holds at most kQuickGather): its wavefronts' parts of the filter's copy, or its
+// tiles of x.
+template <typename T, int BLOCK, int U>
+__device__ inline void quick_gather(const Walk<T> &wk, typename Traits<T>::Key klo,
+                                    typename Traits<T>::Key span, CPS_LDS T *lbuf,
+                                    CPS_LDS uint32_t *lcnt) {
+  using Key = typename Traits<T>::Key;
+  using Vec = typename Traits<T>::Vec;
+  constexpr int V = Traits<T>::kVec;
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const Span<T> &sp = wk.sp;
+  auto one = [&](T v, bool ok) {
+    const bool in = ok & ((Key)(Traits<T>::key(v) - klo) <= span);
+    if (in) {  // (rare)
+      const uint32_t at = atomicAdd((uint32_t *)lcnt, 1u);
+      if (at < (uint32_t)kQuickGather) lbuf[at] = v;
+    }
+  };
+  const int64_t step = wk.wave_mode ? (int64_t)kWave * U : (int64_t)BLOCK * U;
+  const int64_t first = wk.wave_mode ? 0 : (int64_t)blockIdx.x * step;
+  const int64_t stride = wk.wave_mode ? step : (int64_t)gridDim.x * step;
+  const int me = wk.wave_mode ? lane : tid, per = wk.wave_mode ? kWave : BLOCK;
+  for (int64_t base = first; base < sp.nvec; base += stride) {
+    Vec raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t vi = base + (int64_t)u * per + me;
+      raw[u] = sp.V[vi < sp.nvec ? vi : 0];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < V; ++j) one(raw[u][j], base + (int64_t)u * per + me < sp.nvec);
+  }
+  if (sp.nedge > 0 && wk.edge_owner && (wk.wave_mode || tid < kWave)) {
+    const bool have = lane < sp.nedge;
+    one(have ? sp.W[edge_index(sp, lane)] : T(0), have);
+  }
+}
+
+// What follows the filter (quick.hip).  Every workgroup adds the filter's counts and bins by
+// itself (256 counts and 4 x 4096 bins from the caches) and so takes the same decision without
+// waiting: the counts do not prove the interval (0: the general method from pass 0), the rank
+// is a repeated end or its bin one key (1: done), the bin holds at most kQuickGather elements
+// (each workgroup leaves its own in its slot, the last to arrive selects among them; 1: done),
+// or it holds more (2: the general passes go on from the narrowed bracket, over the copy if
+// there is one).  The last to arrive also clears the bins, which all have read by then.
+template <typename T, int BLOCK, int UNROLL>
+__device__ __noinline__ int quick_enter(const SelectArgs<T> &a, Shared<T, BLOCK> &sh) {
+  using Key = typename Traits<T>::Key;
+  constexpr int WPB = BLOCK / kWave;
+  static_assert(BLOCK == 1024 && kHistMaxBins == 4 * BLOCK, "four bins per thread");
+  static_assert(sizeof(sh.ring) / sizeof(T) >= kQuickGather, "the gather's LDS");
+  const int tid = threadIdx.x, wv = tid / kWave, lane = tid % kWave;
+  const int G = gridDim.x, bid = blockIdx.x;
+  const QuickArgs<T> &q = a.quick;
+  const QuickRec rec = *q.rec;
+  auto result = [&](Key key, int64_t less, int64_t equal, int32_t passes, int32_t status) {
+    CpState &s = sh.st;
+    s = CpState{};
+    s.n = a.n;
+    s.passes = passes;
+    s.status = status;
+    s.value = status == ST_OK ? (double)Traits<T>::unkey(key) : __builtin_nan("");
+    s.less = less;
+    s.equal = equal;
+    write_result<T>(a, s);
+  };
+  if (rec.nan) {
+    if (bid == 0 && tid == 0) result(0, 0, 0, 1, ST_NAN);
+    return 1;
+  }
+  // ---- the counts: four fields over the workgroups, the bins of this thread over the copies
+  double f[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int b = tid; b < G; b += BLOCK)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[j] += (double)q.slot[j * q.slot_stride + b];
+  uint32_t h[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int c = 0; c < kQuickCopies; ++c) {
+    const uint4 w = reinterpret_cast<const uint4 *>(q.hist + (int64_t)c * kHistMaxBins)[tid];
+    h[0] += w.x;
+    h[1] += w.y;
+    h[2] += w.z;
+    h[3] += w.w;
+  }
+  if (tid < WPB * kWave) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[j] = wave_sum(f[j]);
+    if (lane == 0) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sh.d[j][wv] = f[j];
+    }
+  }
+  const uint32_t own = h[0] + h[1] + h[2] + h[3];
+  const uint32_t cum = block_scan_u32<BLOCK>(own, sh.rsel.wsum);
+  if (tid == BLOCK - 1) sh.misc[0] = (int64_t)cum + own;
+  __syncthreads();
+  int64_t tot[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    double t = 0.0;
+    for (int w = 0; w < WPB; ++w) t += sh.d[j][w];
+    tot[j] = (int64_t)t;
+  }
+  const int64_t lt = tot[0], ea = tot[1], eb = tot[2], inner = sh.misc[0];
+  const Key ia = (Key)rec.ia, ib = (Key)rec.ib;
+  const int shift = range_shift((uint64_t)(ib - ia), 12);
+  // ---- the decision (uniform over the grid)
+  enum { MISS, NAN_, DONE, GATHER, MORE };
+  int mode = MISS;
+  Key klo = 0, khi = 0;
+  int64_t less = 0, equal = 0, r = a.k - lt;
+  if (tot[3] > 0) {
+    mode = NAN_;
+  } else if (r >= 1 && r <= ea) {
+    mode = DONE;
+    klo = (Key)rec.ka;
+    less = lt;
+    equal = ea;
+  } else if (r > ea && r <= ea + inner) {
+    r -= ea;
+    pick4<BLOCK>(h, cum, (uint32_t)r, 0, sh.rsel);
+    __syncthreads();
+    r -= sh.rsel.below[0];
+    less = lt + ea + sh.rsel.below[0];
+    equal = sh.rsel.inb[0];
+    klo = ia + ((Key)sh.rsel.bin[0] << shift);
+    const Key l = klo + (((Key)1 << shift) - 1);
+    khi = l < ib && l >= klo ? l : ib;
+    mode = klo == khi ? DONE : (equal <= kQuickGather ? GATHER : MORE);
+  } else if (r > ea + inner && r <= ea + inner + eb) {
+    mode = DONE;
+    klo = (Key)rec.kb;
+    less = lt + ea + inner;
+    equal = eb;
+  }
+  if (rec.copied) {
+    if (lane == 0) sh.wseg[0][wv] = q.kept[(int64_t)bid * WPB + wv];
+  }
+  if (tid == 0) sh.lcnt = 0u;
+  __syncthreads();
+  Walk<T> wk;
+  if (mode == GATHER) {
+    CPS_LDS T *lbuf = (CPS_LDS T *)&sh.ring[0][0][0];
+    if (rec.copied) {
+      wk.sp = make_span(q.z0 + ((int64_t)bid * WPB + wv) * q.seg_R, sh.wseg[0][wv]);
+      wk.wave_mode = true;
+      wk.edge_owner = true;
+    } else {
+      wk.sp = make_span(a.x, a.n);
+      wk.wave_mode = false;
+      wk.edge_owner = bid == 0;
+    }
+    quick_gather<T, BLOCK, UNROLL>(wk, klo, khi - klo, lbuf, (CPS_LDS uint32_t *)&sh.lcnt);
+    __syncthreads();
+    const uint32_t got = sh.lcnt < (uint32_t)kQuickGather ? sh.lcnt : (uint32_t)kQuickGather;
+    CPS_GLOBAL T *z = (CPS_GLOBAL T *)(q.zq + (int64_t)bid * kQuickGather);
+    for (uint32_t i = tid; i < got; i += BLOCK) z[i] = lbuf[i];
+    if (tid == 0) q.zcnt[bid] = got;
+    __syncthreads();
+  }
+  if (tid == 0) sh.last = arrive(q.sync, bid, G) ? 1 : 0;
+  __syncthreads();
+  if (sh.last) {
+#pragma unroll
+    for (int c = 0; c < kQuickCopies; ++c)
+      reinterpret_cast<uint4 *>(q.hist + (int64_t)c * kHistMaxBins)[tid] = uint4{0u, 0u, 0u, 0u};
+    if (mode == NAN_ || mode == DONE) {
+      if (tid == 0) result(klo, less, equal, 1, mode == DONE ? ST_OK : ST_NAN);
+    } else if (mode == GATHER) {
+      // element i of the gathered bin is in the slot whose prefix count holds i
+      uint32_t *pre = sh.rh + kHistMaxBins;  // (G <= 1024 <= kHistMaxBins entries)
+      const uint32_t c = tid < G ? q.zcnt[tid] : 0u;
+      const uint32_t at = block_scan_u32<BLOCK>(c, sh.rsel.wsum);
+      pre[tid] = at;
+      if (tid == BLOCK - 1) sh.misc[1] = (int64_t)at + c;
+      __syncthreads();
+      const uint32_t m = (uint32_t)sh.misc[1];
+      constexpr int PER = kQuickGather / BLOCK;
+      Key key[PER];
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        const uint32_t i = (uint32_t)(tid + j * BLOCK);
+        int w = 0;
+#pragma unroll
+        for (int o = 512; o > 0; o >>= 1)
+          if (w + o < G && pre[w + o] <= i) w += o;
+        key[j] = (Key)~(Key)0;
+        if (i < m) key[j] = Traits<T>::key(q.zq[(int64_t)w * kQuickGather + (i - pre[w])]);
+      }
+      if (m != (uint32_t)equal) {  // (the data and the counts disagree)
+        if (tid == 0) result(0, 0, 0, 1, ST_INTERNAL);
+      } else {
+        const RegSel<Key> rs = regs_select<T, BLOCK, PER>(key, (uint32_t)r, m, klo, khi, sh.rh,
+                                                          sh.rsel);
+        if (tid == 0) result(rs.key, less + rs.less, rs.equal, rec.copied ? 1 : 2, ST_OK);
+      }
+    }
+  }
+  if (mode != MISS && mode != MORE) return 1;
+  if (lane == 0 && mode == MISS) sh.wseg[0][wv] = 0;
+  if (mode == MISS) return 0;
+  __syncthreads();
+  if (tid == 0) {
+    const bool ok = cp_quick_state(sh.st, a.n, a.k, (uint64_t)klo, (uint64_t)khi, less, equal,
+                                   rec.copied ? inner : -1, a.cfg);
+    sh.misc[2] = ok ? 2 : 0;
+  }
+  __syncthreads();
+  if (lane == 0 && sh.misc[2] == 0) sh.wseg[0][wv] = 0;
+  return (int)sh.misc[2];
+}
+
 template <typename T, int BLOCK, int UNROLL>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_vgpr(128))) void cp_select_kernel(SelectArgs<T> a) {
   __shared__ Shared<T, BLOCK> sh;
@@ -1713,6 +1992,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_vgpr(128))) void c
   const int G = gridDim.x, bid = blockIdx.x;
   uint32_t gen = 0;
   if (tid == 0) sh.args = a;  // (read by last_update, after the pass's barriers)
+  if (lane == 0) sh.wseg[0][wv] = sh.wseg[1][wv] = 0;
+  int entered = 0;
+  if (a.quick.rec) {  // (uniform) after the filter: nearly always done here
+    __syncthreads();
+    entered = quick_enter<T, BLOCK, UNROLL>(sh.args, sh);
+    if (entered == 1) return;
+    __syncthreads();
+  }
   if (tid == 0) {
     gen = load_relaxed(&a.sync->gen);
     if (bid == 0) {
@@ -1723,8 +2010,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_vgpr(128))) void c
       if (a.stats) a.stats->t_start = wall_clock64();
     }
   }
-  if (lane == 0) sh.wseg[0][wv] = sh.wseg[1][wv] = 0;
-  int phase = PH_PASS0;
+  int phase = entered == 2 ? sh.st.phase : PH_PASS0;
   bool p0_slow = false;
   for (;;) {
     double dv[8];
