@@ -177,16 +177,112 @@ __device__ inline RegSel<typename Traits<T>::Key> regs_select(
   return {(Key)sh.key, base + sh.less, sh.equal};
 }
 
-// ------------------------------------------------------------------ the sample's ends
+__device__ inline void write_selection(cps_result *out, uint64_t bits, double value, int64_t less,
+                                       int64_t equal, int64_t n, int32_t passes, int32_t status) {
+  cps_result r;
+  r.value_bits = bits;
+  r.value = value;
+  r.less = less;
+  r.equal = equal;
+  r.greater = status == ST_OK ? n - less - equal : 0;
+  r.passes = passes;
+  r.status = status;
+  *out = r;
+}
+// ... of the element with this key, or of NaN.
+template <typename T>
+__device__ inline void write_key(cps_result *out, typename Traits<T>::Key key, int64_t less,
+                                 int64_t equal, int64_t n, int32_t passes, bool nan) {
+  const T v = nan ? (T)__builtin_nan("") : Traits<T>::unkey(key) + T(0);
+  uint64_t bits;
+  if (sizeof(T) == 4) bits = (uint64_t)__builtin_bit_cast(uint32_t, (float)v);
+  else bits = __builtin_bit_cast(uint64_t, (double)v);
+  write_selection(out, bits, (double)v, nan ? 0 : less, nan ? 0 : equal, n, passes,
+                  nan ? ST_NAN : ST_OK);
+}
+
+// A value every lane of the wavefront holds, moved to scalar registers.
+__device__ inline float uniform_value(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ inline double uniform_value(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
 
 template <typename Key> struct SampleEnds {
   Key ka, kb;  // the likely interval, as closed keys
   Key ia, ib;  // ... without an end that is one repeated value (its elements are counted apart)
 };
 
+// ------------------------------------------------------------------ the filter's inner loop
+
+// One wavefront's elements against a likely interval, a vector per lane at a time.  Per vector
+// only comparisons, scalar counts and one LDS write of the vectors that hold an inside element
+// (a tenth to a fifth of them); 64 of these at a time are taken apart element by element, by full
+// lanes.  Masks are combined as scalars: per-lane booleans cost two vector instructions each time
+// they become a mask.  (Element by element, each with its own branch, the loop took 105 cycles
+// per 64 elements and SIMD at 4 to 6 wavefronts, whatever the memory did.)
+template <typename T> struct RowFilter {
+  using Vec = typename Traits<T>::Vec;
+  static constexpr int V = Traits<T>::kVec;
+  static constexpr uint32_t kRows = 2 * kWave;  // LDS vectors per wavefront
+  T va, vb, wa, wb;      // the interval's ends, and without repeated ends (uniform)
+  bool ties;             // they differ (uniform)
+  uint64_t below, ea, eb;  // per wavefront: below wa, of these equal to va, above wb equal to vb
+  uint32_t held;
+  CPS_LDS Vec *buf;
+
+  __device__ inline RowFilter(const SampleEnds<typename Traits<T>::Key> &e, Vec *lds) {
+    va = uniform_value(Traits<T>::unkey(e.ka));
+    vb = uniform_value(Traits<T>::unkey(e.kb));
+    wa = uniform_value(Traits<T>::unkey(e.ia));
+    wb = uniform_value(Traits<T>::unkey(e.ib));
+    ties = __builtin_amdgcn_readfirstlane(e.ia != e.ka || e.ib != e.kb) != 0;
+    below = ea = eb = 0;
+    held = 0;
+    buf = (CPS_LDS Vec *)lds;
+  }
+  __device__ inline uint64_t outside(T v, uint64_t ok) {
+    const uint64_t lo = ballot(v < wa), hi = ballot(v > wb);
+    below += popc(lo & ok);
+    if (ties) {
+      ea += popc(lo & ~ballot(v < va) & ok);
+      eb += popc(hi & ~ballot(v > vb) & ok);
+    }
+    return lo | hi;
+  }
+  // A vector per lane (those of the mask): put(v, mask) gets inside elements when 64 are held.
+  template <typename Put> __device__ inline void row(Vec v, uint64_t ok, Put &&put) {
+    uint64_t out = ~0ull;
+#pragma unroll
+    for (int j = 0; j < V; ++j) out &= outside(v[j], ok);
+    const uint64_t m = ok & ~out;
+    if (__builtin_amdgcn_inverse_ballot_w64(m)) buf[held + lane_rank(m)] = v;
+    held += popc(m);
+    if (held >= (uint32_t)kWave) drain(kWave, put);
+  }
+  // The last m (<= 64) vectors held.
+  template <typename Put> __device__ inline void drain(uint32_t m, Put &&put) {
+    __builtin_amdgcn_wave_barrier();
+    held -= m;
+    const int lane = threadIdx.x % kWave;
+    const Vec v = buf[held + lane];
+    const uint64_t ok = m >= (uint32_t)kWave ? ~0ull : (1ull << m) - 1ull;
+#pragma unroll
+    for (int j = 0; j < V; ++j) put(v[j], ok & ~(ballot(v[j] < wa) | ballot(v[j] > wb)));
+    __builtin_amdgcn_wave_barrier();
+  }
+};
+
+// ------------------------------------------------------------------ the sample's ends
+
+
 // The likely interval of rank k of n values from S of their keys, PER per thread in registers
 // (S = BLOCK PER; no NaN): the bins of sample ranks floor(q - d) and ceil(q + d), q = S p, p = (k -
-// 1/2) / n, d = 4 sqrt(S p (1 - p)) + 2 (four binomial standard deviations), each end's bin
+// 1/2) / n, d = dev sqrt(S p (1 - p)) + 2 (dev binomial standard deviations), each end's bin
 // split again (2 BLOCK sub-bins) until it holds at most a sixteenth of the samples between the
 // ranks or is one key (a value that repeats).  An end whose rank falls outside the sample is
 // open: the key of -inf or +inf.  Every workgroup that calls it on the same sample gets the
@@ -194,13 +290,14 @@ template <typename Key> struct SampleEnds {
 template <typename T, int BLOCK, int PER>
 __device__ inline SampleEnds<typename Traits<T>::Key> sample_ends(
     const typename Traits<T>::Key (&v)[PER], typename Traits<T>::Key klo,
-    typename Traits<T>::Key khi, int64_t n, int64_t k, uint32_t *hist, RegSelShared<BLOCK> &sh) {
+    typename Traits<T>::Key khi, int64_t n, int64_t k, double dev, uint32_t *hist,
+    RegSelShared<BLOCK> &sh) {
   using Key = typename Traits<T>::Key;
   constexpr int kBinsLog2 = BLOCK == 1024 ? 12 : (BLOCK == 512 ? 11 : 10);
   constexpr uint32_t S = BLOCK * PER;
   const int tid = threadIdx.x;
   const double Sd = (double)S, p = ((double)k - 0.5) / (double)n;
-  const double q = Sd * p, d = 4.0 * __builtin_sqrt(Sd * p * (1.0 - p)) + 2.0;
+  const double q = Sd * p, d = dev * __builtin_sqrt(Sd * p * (1.0 - p)) + 2.0;
   const double r0 = __builtin_floor(q - d), r1 = __builtin_ceil(q + d);
   const bool open0 = r0 < 1.0, open1 = r1 > Sd;
   const uint32_t rank0 = open0 ? 1u : (uint32_t)r0, rank1 = open1 ? S : (uint32_t)r1;

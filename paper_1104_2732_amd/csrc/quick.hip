@@ -16,19 +16,6 @@
 
 namespace cps {
 
-__device__ inline void write_selection(cps_result *out, uint64_t bits, double value, int64_t less,
-                                       int64_t equal, int64_t n, int32_t passes, int32_t status) {
-  cps_result r;
-  r.value_bits = bits;
-  r.value = value;
-  r.less = less;
-  r.equal = equal;
-  r.greater = status == ST_OK ? n - less - equal : 0;
-  r.passes = passes;
-  r.status = status;
-  *out = r;
-}
-
 // ------------------------------------------------------------------ one workgroup
 
 // n <= BLOCK PER elements, all in registers: the key range, then histograms of the keys until
@@ -65,41 +52,27 @@ __global__ __launch_bounds__(BLOCK) void quick_small_kernel(const T *__restrict_
   }
   nan = block_key_range<BLOCK>(mn, mx, nan, sh);
   if (nan) {  // (uniform)
-    if (tid == 0) {
-      const T q = (T)__builtin_nan("") + T(0);
-      uint64_t bits;
-      if (sizeof(T) == 4) bits = (uint64_t)__builtin_bit_cast(uint32_t, (float)q);
-      else bits = __builtin_bit_cast(uint64_t, (double)q);
-      write_selection(out, bits, (double)q, 0, 0, n, 1, ST_NAN);
-    }
+    if (tid == 0) write_key<T>(out, 0, 0, 0, n, 1, true);
     return;
   }
   const RegSel<Key> r =
       regs_select<T, BLOCK, PER>(key, (uint32_t)k, (uint32_t)n, mn, mx, hist, sh);
-  if (tid == 0) {
-    const T val = Traits<T>::unkey(r.key) + T(0);
-    uint64_t bits;
-    if (sizeof(T) == 4) bits = (uint64_t)__builtin_bit_cast(uint32_t, (float)val);
-    else bits = __builtin_bit_cast(uint64_t, (double)val);
-    write_selection(out, bits, (double)val, r.less, r.equal, n, 1, ST_OK);
-  }
+  if (tid == 0) write_key<T>(out, r.key, r.less, r.equal, n, 1, false);
 }
 
 // ------------------------------------------------------------------ the filter
 
 // Pass 0 of the one-read selection over x (n elements, at least the sample's 1024 SPER): every
 // workgroup takes the sample and its ends by itself (the same everywhere, so nothing waits),
-// then its tiles of x as the general kernel deals them.  Per element only two comparisons and a
-// place in the wavefront's LDS buffer for those inside; the buffer is emptied 64 at a time, by
-// full wavefronts: NaN found, the key's bin counted and, with COPY, one contiguous store to the
-// wavefront's region of the split buffer (the region holds the wavefront's whole share, so the
-// copy always fits).  An end that is one repeated value is counted apart, by one comparison
-// more, and neither binned nor copied.
+// then its tiles of x as the general kernel deals them (RowFilter).  An inside element that is NaN
+// is counted, any other's key bin is, and with COPY all go to the wavefront's region of the split
+// buffer (which holds the wavefront's whole share, so the copy always fits).  An end that is one
+// repeated value is counted apart, by comparisons, and neither binned nor copied.
 //
-// Bound: HBM for float64, issue for float32.  ~3 % of the elements are inside (4 deviations of a
-// 16384 sample either way), but nearly every 64 hold one: binning and copying them where they are
-// found cost 35 instructions per 64 elements (2^28 float32: 285 us a call), left to full
-// wavefronts it is 231 us (4.6 TB/s).
+// Bound: HBM.  2^28 float32 197 us, float64 391 us; without the copy's stores 172 and 332, which is
+// the sample (9 us) and the read (158 us per GiB): the ~3 % of the elements that are inside (4
+// deviations of a 16384 sample either way) are cheap to find, but writing them between reads
+// costs five times their share of the traffic.
 constexpr int kQuickBlock = kSelectBlock;
 constexpr int kQuickU = kSelectUnroll;
 
@@ -108,11 +81,10 @@ __global__ __launch_bounds__(kQuickBlock) __attribute__((amdgpu_num_vgpr(128)))
 void quick_filter_kernel(QuickArgs<T> a) {
   using Key = typename Traits<T>::Key;
   using Vec = typename Traits<T>::Vec;
-  constexpr int V = Traits<T>::kVec, U = kQuickU, BLOCK = kQuickBlock, NW = BLOCK / kWave;
-  constexpr uint32_t kBuf = (V + 1) * kWave;  // (below 64 held before a vector)
+  constexpr int U = kQuickU, BLOCK = kQuickBlock, NW = BLOCK / kWave;
   __shared__ uint32_t hist[kHistMaxBins];
   __shared__ RegSelShared<BLOCK> sh;
-  __shared__ T buf[NW][kBuf];
+  __shared__ Vec buf[NW][RowFilter<T>::kRows];
   __shared__ unsigned long long scount[4];  // below, the ends' repeated values, NaN
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -144,7 +116,7 @@ void quick_filter_kernel(QuickArgs<T> a) {
     if (bid == 0 && tid == 0) a.rec->nan = 1;
     return;
   }
-  const SampleEnds<Key> e = sample_ends<T, BLOCK, SPER>(sk, mn, mx, a.n, a.k, hist, sh);
+  const SampleEnds<Key> e = sample_ends<T, BLOCK, SPER>(sk, mn, mx, a.n, a.k, 4.0, hist, sh);
   if (bid == 0 && tid == 0) {
     QuickRec r;
     r.ka = (uint64_t)e.ka;
@@ -155,93 +127,64 @@ void quick_filter_kernel(QuickArgs<T> a) {
     r.copied = COPY ? 1 : 0;
     *a.rec = r;
   }
-  const T va = Traits<T>::unkey(e.ka), vb = Traits<T>::unkey(e.kb);
-  const T wa = Traits<T>::unkey(e.ia), wb = Traits<T>::unkey(e.ib);
-  const bool ties = e.ia != e.ka || e.ib != e.kb;  // (uniform)
   const int shift = range_shift((uint64_t)(e.ib - e.ia), 12);
   *reinterpret_cast<uint4 *>(&hist[4 * tid]) = uint4{0u, 0u, 0u, 0u};
   if (tid < 4) scount[tid] = 0ull;
   __syncthreads();
-  uint64_t below = 0, ea = 0, eb = 0;  // per wavefront (scalar): below ia, the repeated ends
-  uint32_t nn = 0;                     // per lane: NaN
-  uint32_t held = 0, out = 0;          // per wavefront: in the LDS buffer, in the region
+  RowFilter<T> f(e, buf[wv]);
+  uint32_t nn = 0;   // per lane: NaN
+  uint32_t out = 0;  // per wavefront: in the region
   CPS_GLOBAL T *region = nullptr;
   if (COPY) region = (CPS_GLOBAL T *)uniform_ptr(a.z0 + ((int64_t)bid * NW + wv) * a.seg_R);
-  auto drain = [&](uint32_t m) {  // the buffer's last m elements (m <= 64)
-    __builtin_amdgcn_wave_barrier();
-    held -= m;
-    const bool have = (uint32_t)lane < m;
-    const T w = buf[wv][held + lane];
-    const bool num = w == w;
-    nn += (have & !num) ? 1u : 0u;
-    if (have & num) atomicAdd(&hist[(uint32_t)((Traits<T>::key(w) - e.ia) >> shift)], 1u);
-    if (COPY) {
-      if (have) region[out + lane] = w;
-      out += m;
+  auto put = [&](T v, uint64_t m) {
+    const bool num = v == v;
+    if (__builtin_amdgcn_inverse_ballot_w64(m)) {
+      nn += num ? 0u : 1u;
+      if (num) atomicAdd(&hist[(uint32_t)((Traits<T>::key(v) - e.ia) >> shift)], 1u);
+      if (COPY) region[out + lane_rank(m)] = v;
     }
-    __builtin_amdgcn_wave_barrier();
-  };
-  auto one = [&](T v, bool valid) {
-    const uint64_t ok = ballot(valid);
-    const uint64_t lo = ballot(v < wa), hi = ballot(v > wb);
-    below += popc(lo & ok);
-    if (ties) {
-      ea += popc(lo & ~ballot(v < va) & ok);
-      eb += popc(hi & ~ballot(v > vb) & ok);
-    }
-    const uint64_t m = ok & ~(lo | hi);
-    if (m & (1ull << lane)) buf[wv][held + lane_rank(m)] = v;
-    held += popc(m);
+    if (COPY) out += popc(m);
   };
   const Span<T> sp = make_span(a.x, a.n);
   const int64_t step = (int64_t)BLOCK * U, hop = (int64_t)G * step;
   int64_t base = (int64_t)bid * step;
-  const int64_t last_full = sp.nvec - step;
-  if (base <= last_full) {
-    Vec cur[U];
+  Vec cur[U];
+  auto load = [&](int64_t at) {  // (places past the end: the first vector)
 #pragma unroll
-    for (int u = 0; u < U; ++u) cur[u] = __builtin_nontemporal_load(&sp.V[base + u * BLOCK + tid]);
-    for (;;) {
-      const int64_t nb = base + hop;
-      const bool more = nb <= last_full;  // (uniform)
-      Vec nxt[U];
-      if (more) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) nxt[u] = __builtin_nontemporal_load(&sp.V[nb + u * BLOCK + tid]);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int j = 0; j < V; ++j) one(cur[u][j], true);
-        while (held >= (uint32_t)kWave) drain(kWave);
-      }
-      base = nb;
-      if (!more) break;
-#pragma unroll
-      for (int u = 0; u < U; ++u) cur[u] = nxt[u];
-    }
-  }
-  for (; base < sp.nvec; base += hop) {  // the last, partial tile
     for (int u = 0; u < U; ++u) {
-      const int64_t vi = base + u * BLOCK + tid;
-      const bool valid = vi < sp.nvec;
-      const Vec w = sp.V[valid ? vi : 0];
-#pragma unroll
-      for (int j = 0; j < V; ++j) one(w[j], valid);
-      while (held >= (uint32_t)kWave) drain(kWave);
+      const int64_t vi = at + u * BLOCK + tid;
+      cur[u] = __builtin_nontemporal_load(&sp.V[vi < sp.nvec ? vi : 0]);
     }
+  };
+  load(base);
+  // Every pass issues the next tile's loads: a conditional load would make the wait before the
+  // current tile's use one for the next tile's first load as well.
+  for (; base + hop + step <= sp.nvec; base += hop) {
+    Vec nxt[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) nxt[u] = __builtin_nontemporal_load(&sp.V[base + hop + u * BLOCK + tid]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) f.row(cur[u], ~0ull, put);
+#pragma unroll
+    for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+  }
+  for (; base < sp.nvec; base += hop) {  // the last one or two tiles
+#pragma unroll
+    for (int u = 0; u < U; ++u) f.row(cur[u], ballot(base + u * BLOCK + tid < sp.nvec), put);
+    load(base + hop);
   }
   if (sp.nedge > 0 && bid == 0 && wv == 0) {  // the unaligned head and tail
-    const bool have = lane < sp.nedge;
-    one(sp.W[have ? edge_index(sp, lane) : 0], have);
+    const uint64_t ok = (1ull << sp.nedge) - 1ull;
+    const T v = sp.W[lane < sp.nedge ? edge_index(sp, lane) : 0];
+    put(v, ok & ~f.outside(v, ok));
   }
-  while (held > 0) drain(held < (uint32_t)kWave ? held : (uint32_t)kWave);
+  if (f.held > 0) f.drain(f.held, put);
   if (COPY && lane == 0) a.kept[(int64_t)bid * NW + wv] = out;
   const double fnn = wave_sum((double)nn);
   if (lane == 0) {
-    atomicAdd(&scount[0], (unsigned long long)(below - ea));
-    if (ea) atomicAdd(&scount[1], (unsigned long long)ea);
-    if (eb) atomicAdd(&scount[2], (unsigned long long)eb);
+    atomicAdd(&scount[0], (unsigned long long)(f.below - f.ea));
+    if (f.ea) atomicAdd(&scount[1], (unsigned long long)f.ea);
+    if (f.eb) atomicAdd(&scount[2], (unsigned long long)f.eb);
     if (fnn > 0.0) atomicAdd(&scount[3], (unsigned long long)fnn);
   }
   __syncthreads();
