@@ -289,7 +289,7 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
   // filter that reads x once.  (A trace describes the cutting plane's passes, so a traced call
   // runs them; ranks 1 and n are pass 0's extremes, already one read: 2^28 float32 198 us.)
   // Median of normal data, this way / the general kernel: float32 2^8 7 / 22 us, 2^14 7 / 55, 2^16
-  // 22 / 59, 2^20 28 / 66, 2^24 45 / 122, 2^28 231 / 454; float64 2^15 18 / 97, 2^28 413 / 808.
+  // 22 / 59, 2^20 28 / 66, 2^24 43 / 122, 2^28 228 / 454; float64 2^15 18 / 97, 2^28 413 / 808.
   const bool plain = stats == nullptr && bracket_dev == nullptr && default_method(opt);
   if (plain && n <= cps::quick_small_max<T>()) {
     const hipError_t e = cps::launch_quick_small<T>(x, n, k, out, stream);
@@ -372,7 +372,8 @@ struct BatchResolved {
   int64_t cap, ws_stride, gb_off;
   int32_t proposal, team_max;
   int64_t team_chunk, team_cap, team_records;
-  size_t wg_off, bytes;  // per-workgroup buffers at wg_off (after the team buffers)
+  size_t wg_off, q_off, bytes;  // per-workgroup buffers at wg_off (after the team buffers), the
+                                // default selection's counters, order and records at q_off
 };
 
 int resolve_batched(cps_handle *h, int dtype, int64_t count, const cps_batch_options *opt,
@@ -420,7 +421,8 @@ int resolve_batched(cps_handle *h, int dtype, int64_t count, const cps_batch_opt
     r.team_records = count < cps::kTeamRecords ? count : cps::kTeamRecords;
   r.wg_off = align_up(sizeof(cps::BatchCtl), 256) +
              align_up((size_t)r.team_records * r.team_cap * es, 256);
-  r.bytes = r.wg_off + (size_t)r.grid * r.ws_stride * es;
+  r.q_off = align_up(r.wg_off + (size_t)r.grid * r.ws_stride * es, 256);
+  r.bytes = r.q_off + cps::batchq_bytes();
   r.cfg = cps::CpConfig{};
   r.cfg.maxit = o.maxit ? o.maxit : 64;
   r.cfg.dtype = dtype;
@@ -432,6 +434,22 @@ int resolve_batched(cps_handle *h, int dtype, int64_t count, const cps_batch_opt
   r.cfg.hist_bits = o.hist_bits;
   r.cfg.count_first = o.count_first ? 1 : 0;
   return CPS_OK;
+}
+
+// Whether the options of a batched call are the defaults (a copy capacity of more than the default
+// asks for no other method: the default selection needs none).
+bool default_batch(const cps_batch_options *o) {
+  if (!o) return true;
+  cps_batch_options d;
+  cps_default_batch_options(&d);
+  return (o->block_threads == 0 || o->block_threads == d.block_threads) && o->blocks_per_cu == 0 &&
+         (o->split_capacity == 0 || o->split_capacity == d.split_capacity) &&
+         (o->final_threshold == 0 || o->final_threshold == d.final_threshold) &&
+         (o->maxit == 0 || o->maxit == d.maxit) && o->partition_fraction == d.partition_fraction &&
+         o->hist_bits == d.hist_bits && o->count_first != 0 && o->proposal == 1 &&
+         (o->blocks_per_array == 0 || o->blocks_per_array == 1) &&
+         (o->elements_per_block == 0 || o->elements_per_block == d.elements_per_block) &&
+         (o->team_capacity == 0 || o->team_capacity >= d.team_capacity);
 }
 
 template <typename T>
@@ -464,8 +482,39 @@ int run_batched(cps_handle *h, const void *const *ptrs, const int64_t *sizes, co
   a.team_records = r.team_records;
   a.teams = h->tws;
   a.ksum = ksum;
-  hipError_t e = cps::launch_batched<T>(a, r.grid, r.block, stream);
-  if (e != hipSuccess) return hip_fail(e);
+  a.list = a.list_count = nullptr;
+  if (!default_batch(opt)) {
+    hipError_t e = cps::launch_batched<T>(a, r.grid, r.block, stream);
+    return e == hipSuccess ? CPS_OK : hip_fail(e);
+  }
+  // The default selection: each array read once; what its counts do not prove is listed and taken
+  // by the general kernel afterwards (which returns at once when the list is empty).
+  const int per_cu = cps::batchq_max_blocks_per_cu<T>();
+  if (per_cu < 1) return CPS_ENODEV;
+  cps::BatchqArgs<T> q;
+  char *qb = (char *)h->bws + r.q_off;
+  q.ctl = (cps::BatchqCtl *)qb;
+  q.slot = (cps::BatchqSlot *)(qb + sizeof(cps::BatchqCtl));
+  q.rec = (cps::BatchqRec *)(q.slot + cps::kBatchSortMax);
+  q.redo = (uint32_t *)(q.rec + cps::kBatchSortMax);
+  q.pool = a.zbuf;
+  q.pool_elems = (int64_t)r.grid * r.ws_stride;
+  a.list = q.redo;
+  a.list_count = &q.ctl->redo;
+  a.team_max = 1;
+  a.team_records = 0;
+  for (int64_t at = 0; at < count; at += cps::kBatchSortMax) {
+    const int64_t m = count - at < cps::kBatchSortMax ? count - at : cps::kBatchSortMax;
+    q.ptrs = a.ptrs = (const T *const *)ptrs + at;
+    q.sizes = a.sizes = sizes + at;
+    q.ks = a.ks = ks + at;
+    q.out = a.out = out + at;
+    q.ksum = a.ksum = ksum ? ksum + at : nullptr;
+    q.count = a.count = m;
+    hipError_t e = cps::launch_batchq<T>(q, h->cu_count * per_cu, stream);
+    if (e == hipSuccess) e = cps::launch_batched<T>(a, r.grid, r.block, stream);
+    if (e != hipSuccess) return hip_fail(e);
+  }
   return CPS_OK;
 }
 

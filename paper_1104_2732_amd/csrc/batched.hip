@@ -953,10 +953,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_vgpr(128)))
 void batched_select_kernel(BatchArgs<T> a) {
   __shared__ BShared<T, BLOCK> sh;
   const int tid = threadIdx.x;
-  const int64_t count = a.count;
+  const int64_t count = a.list ? (int64_t)*a.list_count : a.count;
+  if (a.list && count == 0) return;  // (nothing was left to this kernel; the queue is untouched)
   if (tid == 0) sh.cfg = a.cfg;  // (read after the barriers below)
   // Largest first: every workgroup sorts (size, index) in LDS by itself.
-  const bool sorted = count <= kBatchSortMax;
+  const bool sorted = count <= kBatchSortMax && !a.list;
   if (sorted) {
     int64_t m = 1;
     while (m < count) m <<= 1;
@@ -1014,7 +1015,7 @@ void batched_select_kernel(BatchArgs<T> a) {
           sh.jparts = (int32_t)(nf - f);
         } else {
           sh.jslot = q;
-          sh.jindex = q;
+          sh.jindex = a.list ? (int64_t)a.list[q] : q;
           sh.jpart = 0;
           sh.jparts = 1;
         }

@@ -168,7 +168,48 @@ template <typename T> struct BatchArgs {
   TeamCtl *teams;        // team_records records
   T *tbuf;               // team_records buffers of team_cap elements
   double *ksum;          // per array: the sum of its k smallest elements (or null)
+  const uint32_t *list;  // only these arrays (indices), *list_count of them; or null: all
+  const uint32_t *list_count;
 };
+
+// ---- the default batched selection (batchq.hip)
+// Its workspace: the counters, the arrays in work order, a record per shared array and the list of
+// arrays left to the general kernel.
+struct BatchqCtl {
+  uint32_t items, teams, team_items, pad0[29];
+  uint32_t queue, pad1[31];
+  uint32_t redo, pad2[31];
+};
+struct BatchqSlot {
+  uint64_t x;                // the array
+  int64_t n, k;
+  uint32_t index, first, parts, pad;  // in the caller's order; first work item; work items
+};
+struct BatchqRec {
+  uint64_t cursor;           // elements in the array's region of the copy
+  uint64_t lt, ea, eb;       // #(x < interval), the two ends' repeated values
+  double sum;                // of the elements below the interval
+  int64_t region;            // its region's first element in the pool (-1: none)
+  uint32_t arrived, over;    // parts that are done; a part found no room
+  uint64_t pad;
+};
+template <typename T> struct BatchqArgs {
+  const T *const *ptrs;
+  const int64_t *sizes, *ks;
+  int64_t count;             // at most kBatchSortMax
+  cps_result *out;
+  double *ksum;              // or null
+  BatchqCtl *ctl;
+  BatchqSlot *slot;          // larger size classes first
+  BatchqRec *rec;            // per slot (shared arrays only)
+  uint32_t *redo;
+  T *pool;                   // regions of the arrays that several workgroups share
+  int64_t pool_elems;
+};
+size_t batchq_bytes();       // of ctl, slot, rec and redo, in this order
+template <typename T>
+hipError_t launch_batchq(const BatchqArgs<T> &a, int grid, hipStream_t stream);
+template <typename T> int batchq_max_blocks_per_cu();
 
 template <typename T>
 hipError_t launch_batched(const BatchArgs<T> &a, int grid, int block, hipStream_t stream);
