@@ -536,6 +536,168 @@ __global__ __launch_bounds__(256) void mlp_reduce_kernel(const float *__restrict
   }
 }
 
+// The loss and gradient of a minibatch: four examples per workgroup, one per wavefront, so that
+// 256 examples are 64 workgroups of short chains instead of 8 long ones.  The weights come
+// through LDS: read row by row from memory, a lane's strided loads touch a line each.  Each
+// workgroup leaves its four examples' sums (and the loss in the place after the parameters).
+// Bound: latency, two launches and the chains of 67 and 64 additions (52 -> 15 us for 256
+// examples).
+constexpr int kFewEx = kMlpBlock / kHid;
+struct MlpFewShared {
+  float W1[kHid * kIn];   // (odd row stride)
+  float W2[kHid * kHS];
+  float X[kFewEx][kIn];
+  float H1[kFewEx][kHS], H2[kFewEx][kHS];  // after the ReLU
+  float D2[kFewEx][kHS], D1[kFewEx][kHS];
+  float dO[kFewEx][kOut];
+  float lossv[kFewEx];
+};
+
+__global__ __launch_bounds__(kMlpBlock) void mlp_grad_few_kernel(const float *__restrict__ P,
+                                                                 const float *__restrict__ feat,
+                                                                 const float *__restrict__ ustar,
+                                                                 int64_t count,
+                                                                 float *__restrict__ part) {
+  __shared__ MlpFewShared sh;
+  const int tid = threadIdx.x, j = tid % kHid, e = tid / kHid;
+  const int64_t r0 = (int64_t)blockIdx.x * kFewEx;
+  const int nr = (int)(count - r0 < kFewEx ? count - r0 : kFewEx);
+  const float invB = 1.0f / (float)count;
+  float *G = part + (int64_t)blockIdx.x * (kParams + 1);
+  constexpr int N1 = (kHid * kIn + kMlpBlock - 1) / kMlpBlock, N2 = kHid * kHid / kMlpBlock;
+  constexpr int NX = (kFewEx * kIn + kMlpBlock - 1) / kMlpBlock;
+  float w1[N1], w2[N2], xv[NX];
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    const int q = tid + r * kMlpBlock;
+    xv[r] = feat[r0 * kIn + (q < nr * kIn ? q : 0)];
+  }
+#pragma unroll
+  for (int r = 0; r < N1; ++r) {
+    const int q = tid + r * kMlpBlock;
+    w1[r] = P[kOffW1 + (q < kHid * kIn ? q : 0)];
+  }
+#pragma unroll
+  for (int r = 0; r < N2; ++r) w2[r] = P[kOffW2 + tid + r * kMlpBlock];
+  const float b1 = P[kOffB1 + j], b2 = P[kOffB2 + j];
+  const float w30 = P[kOffW3 + j], w31 = P[kOffW3 + kHid + j];
+  const float b30 = P[kOffB3], b31 = P[kOffB3 + 1];
+  const float target = ustar[r0 + (e < nr ? e : 0)];
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    const int q = tid + r * kMlpBlock;
+    if (q < kFewEx * kIn) sh.X[q / kIn][q % kIn] = q < nr * kIn ? xv[r] : 0.0f;
+  }
+#pragma unroll
+  for (int r = 0; r < N1; ++r) {
+    const int q = tid + r * kMlpBlock;
+    if (q < kHid * kIn) sh.W1[q] = w1[r];
+  }
+#pragma unroll
+  for (int r = 0; r < N2; ++r) {
+    const int q = tid + r * kMlpBlock;
+    sh.W2[q / kHid * kHS + q % kHid] = w2[r];
+  }
+  __syncthreads();
+  // ---- forward (a wavefront's own example: no workgroup barrier needed between layers)
+  float z1 = 0.0f, z2 = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kIn; ++i) z1 = z1 + sh.W1[j * kIn + i] * sh.X[e][i];
+  z1 = z1 + b1;
+  sh.H1[e][j] = relu(z1);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < kHid; ++i) z2 = z2 + sh.W2[j * kHS + i] * sh.H1[e][i];
+  z2 = z2 + b2;
+  const float h2 = relu(z2);
+  sh.H2[e][j] = h2;
+  // ---- the outputs (float products, summed in double), loss and its derivatives
+  const float o0 = (float)(wave_sum((double)(w30 * h2)) + (double)b30);
+  const float sv = (float)(wave_sum((double)(w31 * h2)) + (double)b31);
+  const float d = o0 - target;
+  const bool in_clamp = sv > kLogWMin && sv < kLogWMax;
+  const float w = expf(fminf(fmaxf(sv, kLogWMin), kLogWMax));
+  const float ad = fabsf(d);
+  const bool out_cov = ad > w;
+  const float sgn = d > 0.0f ? 1.0f : (d < 0.0f ? -1.0f : 0.0f);
+  const float d0 = (2.0f * kCSq * d + (out_cov ? kCCov * sgn : 0.0f)) * invB;
+  const float d1 = in_clamp ? ((out_cov ? -kCCov : 0.0f) + kCW) * w * invB : 0.0f;
+  if (j == 0) {
+    sh.lossv[e] = (kCSq * d * d + kCCov * (out_cov ? ad - w : 0.0f) + kCW * w) * invB;
+    sh.dO[e][0] = d0;
+    sh.dO[e][1] = d1;
+  }
+  // ---- backward
+  sh.D2[e][j] = z2 > 0.0f ? d0 * w30 + d1 * w31 : 0.0f;
+  __builtin_amdgcn_wave_barrier();
+  float g = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kHid; ++i) g = g + sh.D2[e][i] * sh.W2[i * kHS + j];
+  sh.D1[e][j] = z1 > 0.0f ? g : 0.0f;
+  __syncthreads();
+  // ---- the examples' sums, in example order
+  auto over = [&](auto &&term) {
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kFewEx; ++i)
+      if (i < nr) s = s + term(i);  // (uniform)
+    return s;
+  };
+#pragma unroll
+  for (int r = 0; r < N1; ++r) {
+    const int q = tid + r * kMlpBlock;
+    if (q < kHid * kIn) {
+      const int row = q / kIn, col = q % kIn;
+      G[kOffW1 + q] = over([&](int i) { return sh.D1[i][row] * sh.X[i][col]; });
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < N2; ++r) {
+    const int q = tid + r * kMlpBlock, row = q / kHid, col = q % kHid;
+    G[kOffW2 + q] = over([&](int i) { return sh.D2[i][row] * sh.H1[i][col]; });
+  }
+  if (e == 0) G[kOffB1 + j] = over([&](int i) { return sh.D1[i][j]; });
+  if (e == 1) G[kOffB2 + j] = over([&](int i) { return sh.D2[i][j]; });
+  if (e >= 2) G[kOffW3 + (e - 2) * kHid + j] = over([&](int i) { return sh.dO[i][e - 2] * sh.H2[i][j]; });
+  if (tid < kOut) G[kOffB3 + tid] = over([&](int i) { return sh.dO[i][tid]; });
+  if (tid == kOut) G[kParams] = over([&](int i) { return sh.lossv[i]; });
+}
+
+// Their sum: 64 places per workgroup, each by 8 threads over an eighth of the workgroups in order,
+// then the eighths in order.
+__global__ __launch_bounds__(512) void mlp_reduce_few_kernel(const float *__restrict__ part, int nwg,
+                                                             float *__restrict__ grad,
+                                                             float *__restrict__ loss) {
+  constexpr int NP = 64, NG = 8, U = 8;
+  __shared__ float sum[NG][NP];
+  const int c = threadIdx.x % NP, g = threadIdx.x / NP;
+  const int p = blockIdx.x * NP + c;
+  const int w0 = (int)((int64_t)nwg * g / NG), w1 = (int)((int64_t)nwg * (g + 1) / NG);
+  const float *src = part + (p <= kParams ? p : 0);
+  float s = 0.0f;
+  for (int w = w0; w < w1; w += U) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = src[(int64_t)(w + u < w1 ? w + u : w0) * (kParams + 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) s = w + u < w1 ? s + v[u] : s;
+  }
+  sum[g][c] = s;
+  __syncthreads();
+  if (g == 0 && p <= kParams) {
+    s = sum[0][c];
+#pragma unroll
+    for (int i = 1; i < NG; ++i) s = s + sum[i][c];
+    if (p < kParams) grad[p] = s;
+    else if (loss) *loss = s;
+  }
+}
+
+// Up to this many examples these kernels are used.  They are faster beyond as well (32 examples 14 / 50
+// us, 256 15 / 52, 1024 20 / 59, 4096 34 / 85, 16384 94 / 200), but leave 34 KB of partial sums per
+// four examples: 35 MB here, eight times what the others need.
+constexpr int64_t kMlpFew = 4096;
+
 hipError_t launch_mlp_forward(const float *P, const float *feat, int64_t count, float *out,
                               hipStream_t stream) {
   const int64_t nwg = (count + kEPW - 1) / kEPW;
@@ -544,13 +706,20 @@ hipError_t launch_mlp_forward(const float *P, const float *feat, int64_t count, 
 }
 
 size_t mlp_grad_workspace(int64_t count) {
-  const int64_t nwg = (count + kEPW - 1) / kEPW;
+  const int64_t per = count <= kMlpFew ? kFewEx : kEPW;
+  const int64_t nwg = (count + per - 1) / per;
   return (size_t)nwg * (kParams + 1) * sizeof(float) + 256;
 }
 
 hipError_t launch_mlp_loss_grad(const float *P, const float *feat, const float *ustar,
                                 int64_t count, float *grad, float *loss, float *ws,
                                 hipStream_t stream) {
+  if (count <= kMlpFew) {
+    const int64_t few = (count + kFewEx - 1) / kFewEx;
+    mlp_grad_few_kernel<<<dim3((unsigned)few), dim3(kMlpBlock), 0, stream>>>(P, feat, ustar, count, ws);
+    mlp_reduce_few_kernel<<<dim3((kParams + 64) / 64), dim3(512), 0, stream>>>(ws, (int)few, grad, loss);
+    return hipGetLastError();
+  }
   const int64_t nwg = (count + kEPW - 1) / kEPW;
   float *part = ws;
   float *part_loss = ws + nwg * kParams;
