@@ -145,7 +145,8 @@ def legs_traffic_from(fetch_dir: str, write_dir: str) -> dict:
                "batched_select_kernel<double": "batched float64 (LMS medians, materialised form)",
                "lms_residual_rows_kernel<8, 2, false>": "LMS residuals (materialised form)",
                "lms_filter_kernel": "LMS filter (filtered form)",
-               "lms_gather_kernel": "LMS packing and select (filtered form)"}
+               "lms_select_kernel": "LMS select (filtered form)",
+               "batchq_kernel<float": "default batched float32"}
     out = {"kernel_source_hash": kernel_source_hash()}
     for counter, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rows = _counter_rows(d, counter)

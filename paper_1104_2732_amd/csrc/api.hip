@@ -584,8 +584,8 @@ int cps_reserve_batched(cps_handle *h, int dtype, const cps_batch_options *opt) 
   return r.team_records > 0 ? ensure_team_records(h, nullptr) : CPS_OK;
 }
 
-// The filtered form's workspace and launches (the handle's lock held): R (m x n), C (m x cap),
-// sampled squares, brackets, segment counts, flags, and with ksum_out the segments' sums and
+// The filtered form's workspace and launches (the handle's lock held): R (m x n), sampled
+// squares, brackets, segment counts, flags, and with ksum_out the segments' sums and
 // m records and sums of its own (the selections then land there, *sel_out and *ksum_out
 // point at them).
 static int lms_filtered_run(cps_handle *h, const double *X_dev, const double *y_dev,
@@ -594,15 +594,12 @@ static int lms_filtered_run(cps_handle *h, const double *X_dev, const double *y_
                             hipStream_t s) {
   const size_t dsz = align_up((size_t)m * 8, 256);
   cps::LmsFilterBufs w;
-  const bool vec = (uintptr_t)X_dev % 16 == 0 && (uintptr_t)y_dev % 16 == 0;
-  cps::lms_filter_shape(n, m, p, vec, h->cu_count, &w.bx, &w.nseg, &w.seg);
-  w.cap = cps::lms_filter_cap(n);
+  cps::lms_filter_shape(n, m, p, h->cu_count, &w.bx, &w.nseg, &w.seg, &w.chunk);
   const bool sums = ksum_out != nullptr;
-  const size_t off_c = align_up((size_t)m * (size_t)n * sizeof(double), 256);
-  const size_t off_rs = off_c + align_up((size_t)m * (size_t)w.cap * sizeof(double), 256);
+  const size_t off_rs = align_up((size_t)m * (size_t)(w.nseg * w.seg) * sizeof(double), 256);
   const size_t off_ab = off_rs + align_up((size_t)m * 16384 * sizeof(double), 256);
-  const size_t off_cnt = off_ab + 2 * dsz;
-  const size_t off_full = off_cnt + align_up((size_t)2 * m * w.nseg * sizeof(uint32_t), 256);
+  const size_t off_info = off_ab + 2 * dsz;
+  const size_t off_full = off_info + align_up((size_t)m * w.nseg * sizeof(uint2), 256);
   const size_t off_psum = off_full + dsz;
   const size_t off_sel = off_psum + (sums ? align_up((size_t)m * w.nseg * sizeof(double), 256) : 0);
   const size_t off_ksum = off_sel + (sums ? align_up((size_t)m * sizeof(cps_result), 256) : 0);
@@ -611,10 +608,9 @@ static int lms_filtered_run(cps_handle *h, const double *X_dev, const double *y_
   if (rc) return rc;
   char *base = (char *)h->lws;
   w.R = (double *)base;
-  w.C = (double *)(base + off_c);
   w.Rs = (double *)(base + off_rs);
   w.ab = (double *)(base + off_ab);
-  w.cnt = (uint32_t *)(base + off_cnt);
+  w.info = (uint2 *)(base + off_info);
   w.full = (int32_t *)(base + off_full);
   w.psum = sums ? (double *)(base + off_psum) : nullptr;
   cps_result *sel = sums ? (cps_result *)(base + off_sel) : out_dev;

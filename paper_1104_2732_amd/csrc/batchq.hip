@@ -38,7 +38,6 @@ template <typename T> constexpr int kBqSmall = kBqBlock * kBqPer<T>;
 constexpr int kBqSmpA = 8;                       // samples per lane: 4096 in all, or
 template <typename T> constexpr int kBqSmpB = sizeof(T) == 4 ? 32 : 16;  // 16384 (8192)
 constexpr int kBqU = 4;                          // vectors per lane and tile
-constexpr uint32_t kBqFinal = 256;               // elements ranked by comparing each with all
 constexpr size_t kBqListBytes = 49152;           // LDS for the inside elements
 constexpr int64_t kBqMaxN = (int64_t)1 << 31;    // larger arrays go to the general kernel
 constexpr double kBqDev = 4.5;  // deviations of the interval's ends: a miss in 10^5 arrays
@@ -52,7 +51,7 @@ template <typename T> CPS_HD inline bool bq_shared(int64_t n) { return n >= kBqS
 // A shared array's region of the pool: room for an eighth of its elements (the interval holds
 // 5 %), then the key bins of each part.
 CPS_HD inline int64_t bq_room(int64_t n) { return (n / 8 + 63) / 64 * 64; }
-constexpr int kBqBins = 4 * kBqBlock, kBqBinsLog2 = 11;
+constexpr int kBqBins = 4 * kBqBlock, kBqBinsLog2 = quick_bins_log2(kBqBlock);
 template <typename T> CPS_HD inline int64_t bq_region(int64_t n, uint32_t parts) {
   return bq_room(n) + (int64_t)parts * (int64_t)(kBqBins * sizeof(uint32_t) / sizeof(T));
 }
@@ -192,10 +191,10 @@ template <typename T> struct BqShared {
   T list[kBqWaves][kBqListBytes / sizeof(T) / kBqWaves];
   typename Traits<T>::Vec rows[kBqWaves][RowFilter<T>::kRows];
   uint32_t hist[kBqBins];
-  typename Traits<T>::Key fin[kBqFinal];
+  typename Traits<T>::Key fin[kWalkFinal];
   uint64_t count[3];  // below, the ends' repeated values
   double wsum[kBqWaves];
-  uint32_t held[kBqWaves], over, item, part, last, cursor;
+  uint32_t held[kBqWaves], over, item, last;
   BatchqSlot slot;
 };
 
@@ -300,81 +299,6 @@ __device__ inline bool bq_ends(const Span<T> &sp, int64_t n, int64_t k, BqShared
   if (block_key_range<kBqBlock>(mn, mx, nan, sh.rs)) return false;
   e = sample_ends<T, kBqBlock, PER>(key, mn, mx, n, k, kBqDev, sh.hist, sh.rs);
   return true;
-}
-
-// The element of rank r (1-based) among the elements that `walk` visits, all with keys in [klo,
-// khi], from their counts in this thread's four key bins (range_shift of the range): the rank's
-// bin, split again while it holds many elements, then ranked by comparing each with all.
-template <typename T, typename Walk>
-__device__ inline void bq_walk_select(Walk &&walk, uint32_t (&h)[4], int64_t r,
-                                      typename Traits<T>::Key klo, typename Traits<T>::Key khi,
-                                      BqShared<T> &sh, typename Traits<T>::Key &key, int64_t &less,
-                                      int64_t &equal) {
-  using Key = typename Traits<T>::Key;
-  const int tid = threadIdx.x;
-  less = 0;
-  int64_t cnt;
-  for (;;) {
-    const int shift = range_shift((uint64_t)(khi - klo), kBqBinsLog2);
-    const uint32_t cum = block_scan_u32<kBqBlock>(h[0] + h[1] + h[2] + h[3], sh.rs.wsum);
-    pick4<kBqBlock>(h, cum, (uint32_t)r, 0, sh.rs);
-    __syncthreads();
-    less += sh.rs.below[0];
-    r -= sh.rs.below[0];
-    cnt = sh.rs.inb[0];
-    const Key lo = klo + ((Key)sh.rs.bin[0] << shift);
-    const Key hi = lo + (((Key)1 << shift) - 1);
-    khi = hi < khi && hi >= lo ? hi : khi;
-    klo = lo;
-    if (klo == khi) {
-      key = klo;
-      equal = cnt;
-      return;
-    }
-    if (cnt <= (int64_t)kBqFinal) break;
-    const int next = range_shift((uint64_t)(khi - klo), kBqBinsLog2);
-    __syncthreads();
-    *reinterpret_cast<uint4 *>(&sh.hist[4 * tid]) = uint4{0u, 0u, 0u, 0u};
-    __syncthreads();
-    walk([&](T v, bool ok) {
-      const Key d = Traits<T>::key(v) - klo;
-      if (ok & (d <= khi - klo)) atomicAdd(&sh.hist[(uint32_t)(d >> next)], 1u);
-    });
-    __syncthreads();
-    const uint4 q = *reinterpret_cast<const uint4 *>(&sh.hist[4 * tid]);
-    h[0] = q.x;
-    h[1] = q.y;
-    h[2] = q.z;
-    h[3] = q.w;
-  }
-  if (tid == 0) sh.cursor = 0u;
-  __syncthreads();
-  walk([&](T v, bool ok) {
-    const Key q = Traits<T>::key(v), d = q - klo;
-    if (ok & (d <= khi - klo)) {
-      const uint32_t at = atomicAdd(&sh.cursor, 1u);
-      if (at < kBqFinal) sh.fin[at] = q;
-    }
-  });
-  __syncthreads();
-  if (tid < (int)cnt) {
-    const Key mine = sh.fin[tid];
-    uint32_t lo = 0, eq = 0;
-    for (int i = 0; i < (int)cnt; ++i) {
-      const Key o = sh.fin[i];
-      lo += o < mine ? 1u : 0u;
-      eq += o == mine ? 1u : 0u;
-    }
-    if ((int64_t)lo < r && r <= (int64_t)(lo + eq)) {  // (one key: all its threads write the same)
-      sh.rs.key = (uint64_t)mine;
-      sh.rs.less = lo;
-      sh.rs.equal = eq;
-    }
-  }
-  __syncthreads();
-  key = (Key)sh.rs.key;
-  less += sh.rs.less;
-  equal = sh.rs.equal;
 }
 
 // One part (of `parts`) of an array that does not fit the registers; rec: a shared array's record.
@@ -593,10 +517,10 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
       lsum += ok && (ri > inner || Traits<T>::key(v) < key) ? (double)v : 0.0;
     };
     if (rec) {
-      bq_walk_select<T>(region_walk, h, rank, e.ia, e.ib, sh, key, less, equal);
+      walk_select<T, BLOCK>(region_walk, h, rank, e.ia, e.ib, sh.hist, sh.fin, sh.rs, key, less, equal);
       if (SUM) region_walk(add_inside);
     } else {
-      bq_walk_select<T>(seg_walk, h, rank, e.ia, e.ib, sh, key, less, equal);
+      walk_select<T, BLOCK>(seg_walk, h, rank, e.ia, e.ib, sh.hist, sh.fin, sh.rs, key, less, equal);
       if (SUM) seg_walk(add_inside);
     }
     if (SUM) lsum = bq_sum<T>(lsum, sh);

@@ -220,22 +220,19 @@ hipError_t launch_lms_residuals(const double *X, const double *y, const double *
                                 int64_t *sizes, int64_t *ks, int cu_count, hipStream_t stream);
 // The filtered least-median-of-squares form: the workspace's parts (device memory) and shape.
 struct LmsFilterBufs {
-  double *R;             // m x n: each candidate's kept squares by segment; the whole array
-                         // of a candidate whose bracket missed
-  double *C;             // m x cap: each candidate's kept squares, packed
-  int64_t cap;
+  double *R;             // m x nseg seg: the kept squares, in regions by segment and chunk of candidates;
+                         // then the whole arrays of the candidates whose bracket missed
   double *Rs;            // m x S: the squares of the sampled rows (S <= 16384)
   double *ab;            // 2m: the sampled brackets
-  uint32_t *cnt;         // 2 x m x nseg: kept and #(r <= a) per candidate and segment
-  double *psum;          // m x nseg: the sum of the r <= a per candidate and segment (with
-                         // the trimmed sums only)
+  uint2 *info;           // nseg x m: a segment's and candidate's first kept square in its region;
+                         // their number, and #(r <= a) in the upper half
+  double *psum;          // nseg x m: the sum of the r <= a (with the trimmed sums only)
   int32_t *full;         // m: 1 where the candidate's whole array is formed and selected
-  int64_t bx, nseg, seg;  // the fallback kernel's workgroups per candidate group; segments
-                          // per candidate and rows per segment of the filter
+  int64_t bx, nseg, seg, chunk;  // the fallback kernel's workgroups per candidate group; the
+                         // filter's segments, rows per segment and candidates per chunk
 };
-void lms_filter_shape(int64_t n, int64_t m, int32_t p, bool vec, int cu_count, int64_t *bx,
-                      int64_t *nseg, int64_t *seg);
-int64_t lms_filter_cap(int64_t n);
+void lms_filter_shape(int64_t n, int64_t m, int32_t p, int cu_count, int64_t *bx, int64_t *nseg,
+                      int64_t *seg, int64_t *chunk);
 // Every kernel of the filtered form; the medians land in out (m records).
 // ksum (or null): m doubles, each candidate's sum of its `rank` smallest squares.
 hipError_t launch_lms_filtered(const double *X, const double *y, const double *betas, int64_t n,

@@ -201,6 +201,87 @@ __device__ inline void write_key(cps_result *out, typename Traits<T>::Key key, i
                   nan ? ST_NAN : ST_OK);
 }
 
+// The element of rank r (1-based) among the elements that `walk` visits, all with keys in [klo,
+// khi], from their counts in this thread's four key bins (range_shift of the range): the rank's
+// bin, split again while it holds many elements, then ranked by comparing each with all.
+// `hist` is 4 BLOCK words of LDS, `fin` kWalkFinal keys.
+constexpr uint32_t kWalkFinal = 256;
+CPS_HD constexpr int quick_bins_log2(int block) { return block == 1024 ? 12 : (block == 512 ? 11 : 10); }
+template <typename T, int BLOCK, typename Walk>
+__device__ inline void walk_select(Walk &&walk, uint32_t (&h)[4], int64_t r,
+                                   typename Traits<T>::Key klo, typename Traits<T>::Key khi,
+                                   uint32_t *hist, typename Traits<T>::Key *fin,
+                                   RegSelShared<BLOCK> &sh, typename Traits<T>::Key &key,
+                                   int64_t &less, int64_t &equal) {
+  using Key = typename Traits<T>::Key;
+  const int tid = threadIdx.x;
+  less = 0;
+  int64_t cnt = 0;
+  // (each round narrows the range by the bins' bits: seven at most)
+  for (int round = 0; round < 8; ++round) {
+    const int shift = range_shift((uint64_t)(khi - klo), quick_bins_log2(BLOCK));
+    const uint32_t cum = block_scan_u32<BLOCK>(h[0] + h[1] + h[2] + h[3], sh.wsum);
+    pick4<BLOCK>(h, cum, (uint32_t)r, 0, sh);
+    __syncthreads();
+    less += sh.below[0];
+    r -= sh.below[0];
+    cnt = sh.inb[0];
+    const Key lo = klo + ((Key)sh.bin[0] << shift);
+    const Key hi = lo + (((Key)1 << shift) - 1);
+    khi = hi < khi && hi >= lo ? hi : khi;
+    klo = lo;
+    if (klo == khi) {
+      key = klo;
+      equal = cnt;
+      return;
+    }
+    if (cnt <= (int64_t)kWalkFinal) break;
+    const int next = range_shift((uint64_t)(khi - klo), quick_bins_log2(BLOCK));
+    __syncthreads();
+    *reinterpret_cast<uint4 *>(&hist[4 * tid]) = uint4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    walk([&](T v, bool ok) {
+      const Key d = Traits<T>::key(v) - klo;
+      if (ok & (d <= khi - klo)) atomicAdd(&hist[(uint32_t)(d >> next)], 1u);
+    });
+    __syncthreads();
+    const uint4 q = *reinterpret_cast<const uint4 *>(&hist[4 * tid]);
+    h[0] = q.x;
+    h[1] = q.y;
+    h[2] = q.z;
+    h[3] = q.w;
+  }
+  if (cnt > (int64_t)kWalkFinal) cnt = kWalkFinal;
+  if (tid == 0) sh.cursor = 0u;
+  __syncthreads();
+  walk([&](T v, bool ok) {
+    const Key q = Traits<T>::key(v), d = q - klo;
+    if (ok & (d <= khi - klo)) {
+      const uint32_t at = atomicAdd(&sh.cursor, 1u);
+      if (at < kWalkFinal) fin[at] = q;
+    }
+  });
+  __syncthreads();
+  if (tid < (int)cnt) {
+    const Key mine = fin[tid];
+    uint32_t lo = 0, eq = 0;
+    for (int i = 0; i < (int)cnt; ++i) {
+      const Key o = fin[i];
+      lo += o < mine ? 1u : 0u;
+      eq += o == mine ? 1u : 0u;
+    }
+    if ((int64_t)lo < r && r <= (int64_t)(lo + eq)) {  // (one key: all its threads write the same)
+      sh.key = (uint64_t)mine;
+      sh.less = lo;
+      sh.equal = eq;
+    }
+  }
+  __syncthreads();
+  key = (Key)sh.key;
+  less += sh.less;
+  equal = sh.equal;
+}
+
 // A value every lane of the wavefront holds, moved to scalar registers.
 __device__ inline float uniform_value(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));

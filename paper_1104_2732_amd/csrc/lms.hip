@@ -9,16 +9,15 @@
 // Two forms.  The materialised form writes every square candidate-major in the workspace,
 // one array of n per candidate, and the batched kernel selects rank floor((n+1)/2) of every
 // array.  The filtered form never writes the whole arrays: a first kernel takes each
-// candidate's sampled bracket (a, b) from the squares of a fixed sample of rows (the rows
-// the batched kernel would sample), the filter kernel forms every square once and keeps
-// only those in (a, b), with #(r <= a), and a gather kernel packs the kept squares of each
-// candidate into one array.  Where #(r <= a) < k <= #(r <= a) + #(a < r < b) the k-th
-// smallest of all n squares is the (k - #(r <= a))-th smallest of the kept ones, found by
-// the batched kernel; a candidate whose bracket misses (or whose kept squares exceed the
-// packed array's room) gets its full array written and selected as in the materialised
-// form.  Both give the same value and counts.
+// candidate's sampled bracket (a, b) from the squares of a fixed sample of rows, the filter
+// kernel forms every square once and keeps only those in (a, b), with #(r <= a), and a select
+// kernel reads the kept squares of each candidate.  Where #(r <= a) < k <= #(r <= a) +
+// #(a < r < b) the k-th smallest of all n squares is the (k - #(r <= a))-th smallest of the
+// kept ones; a candidate whose bracket misses gets its full array written and selected as in
+// the materialised form.  Both give the same value and counts.
 #include "cps_device.h"
 #include "cps_kernels.h"
+#include "cps_quick.h"
 #include "cps_sample.h"
 #include "cps_wgsel.h"
 
@@ -166,225 +165,200 @@ __device__ __forceinline__ double sq_residual(const double *row, double yi, cons
   return d * d;
 }
 
-// The squares of the sampled rows (the rows the batched kernel samples in an array of n
-// elements: runs of kPropRun neighbours at sample_stride apart), one candidate per lane as in
-// the filter, to Rs[c * S + i].
+// The three kernels below give a lane a row (T rows: 64 neighbours per T) and loop over the
+// candidates, whose coefficients are scalar loads.  A candidate per lane instead (rows by scalar
+// loads) left most lanes idle with few candidates, and every lane appended to its own candidate's
+// array: a branch for each square, and 8-byte stores into 64 arrays at a time.
+template <int P> constexpr int kLmsTiles = P <= 10 ? 4 : 2;
+constexpr int64_t lms_seg(int p) { return kWave * (p <= 10 ? 4 : 2); }
+
+// The squares of the sampled rows (runs of kPropRun neighbours at sample_stride apart), to
+// Rs[c * S + i].
 template <int P>
-__global__ __launch_bounds__(kLmsBlock) void lms_sample_kernel(
+__global__ __launch_bounds__(kLmsBlock, 4) void lms_sample_kernel(
     const double *__restrict__ X, const double *__restrict__ y, const double *__restrict__ betas,
-    int64_t n, int32_t p, int64_t m, double *__restrict__ Rs) {
-  constexpr int PM = P > 0 ? P : 16;
-  const int pp = P > 0 ? P : p;
-  const int64_t c = (int64_t)blockIdx.y * kLmsBlock + threadIdx.x;
-  const bool live = c < m;
-  double b[PM];
-#pragma unroll
-  for (int j = 0; j < PM; ++j) b[j] = live && j < pp ? betas[c * pp + j] : 0.0;
+    int64_t n, int64_t m, int64_t chunk, double *__restrict__ Rs) {
+  constexpr int T = kLmsTiles<P>;
+  const int lane = threadIdx.x % kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int S = sample_size(n);
   const int64_t stride = sample_stride(n, S);
-  CPS_GLOBAL double *dst = (CPS_GLOBAL double *)Rs + (live ? c : 0) * S;
-  // each workgroup takes a share of the sample's runs, two rows per step (both rows' scalar
-  // loads issued together)
-  const int runs = S / kPropRun;
-  const int per = (runs + (int)gridDim.x - 1) / (int)gridDim.x;
-  const int r0 = (int)blockIdx.x * per, r1 = r0 + per < runs ? r0 + per : runs;
-  for (int run = r0; run < r1; ++run) {
-    for (int q = 0; q < kPropRun; q += 2) {
-      const int64_t i = (int64_t)run * stride + q;
-      double x0[PM], x1[PM];
+  const int i0 = ((int)blockIdx.x * (kLmsBlock / kWave) + wv) * T * kWave;  // (S is a multiple)
+  if (i0 >= S) return;
+  double x[T][P], yv[T];
 #pragma unroll
-      for (int j = 0; j < PM; ++j) {
-        x0[j] = j < pp ? X[i * pp + j] : 0.0;
-        x1[j] = j < pp ? X[(i + 1) * pp + j] : 0.0;
-      }
-      const double v0 = sq_residual<P>(x0, y[i], b, pp);
-      const double v1 = sq_residual<P>(x1, y[i + 1], b, pp);
-      if (live) {
-        dst[run * kPropRun + q] = v0;
-        dst[run * kPropRun + q + 1] = v1;
-      }
-    }
+  for (int t = 0; t < T; ++t) {
+    const int i = i0 + t * kWave + lane;
+    const int64_t row = (int64_t)(i / kPropRun) * stride + i % kPropRun;
+#pragma unroll
+    for (int j = 0; j < P; ++j) x[t][j] = X[row * P + j];
+    yv[t] = y[row];
+  }
+  const int64_t c0 = (int64_t)blockIdx.y * chunk, c1 = c0 + chunk < m ? c0 + chunk : m;
+  CPS_GLOBAL double *dst = (CPS_GLOBAL double *)Rs + c0 * S + i0 + lane;
+  for (int64_t c = c0; c < c1; ++c) {
+    double b[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) b[j] = betas[c * P + j];
+#pragma unroll
+    for (int t = 0; t < T; ++t) dst[t * kWave] = sq_residual<P>(x[t], yv[t], b, P);
+    dst += S;
   }
 }
 
-constexpr int kLmsBracketBlock = 256;
-struct LmsBracketShared {
-  uint64_t kext[2];
-  int32_t flag;
-  SampleLds smp;
-  uint64_t wsum[kLmsBracketBlock / kWave];
-  uint32_t rh[kHistMaxBins];
-};
-
-// One workgroup per candidate: the sampled bracket of its squared residuals from the sampled
-// squares Rs, to ab[2c], ab[2c+1].  A candidate without one gets (+inf, -inf): the filter
-// then keeps nothing of it but NaN, and the gather sends it down the materialised path.
-__global__ __launch_bounds__(kLmsBracketBlock) void lms_bracket_kernel(
-    const double *__restrict__ Rs, int64_t n, int64_t k, double *__restrict__ ab) {
-  __shared__ LmsBracketShared sh;
+// One workgroup per candidate: the likely interval [ka, kb] of its squares' rank from the sampled
+// squares, in registers (sample_ends, 4.5 deviations: a miss in 10^5, and each costs a select
+// over n), as the open interval (a, b) to ab[2c], ab[2c+1].  A candidate whose sample holds NaN gets
+// (+inf, -inf): the filter then keeps nothing of it but NaN, and it goes down the materialised
+// path.  1024 candidates: 76 us with the samples read again for every histogram, 51 us
+// this way.
+template <int PER>
+__global__ __launch_bounds__(1024) void lms_bracket_kernel(const double *__restrict__ Rs, int64_t n,
+                                                           int64_t k, double *__restrict__ ab) {
+  constexpr int BLOCK = 1024;
+  __shared__ uint32_t hist[4 * BLOCK];
+  __shared__ RegSelShared<BLOCK> sh;
   const int64_t c = blockIdx.x;
-  const int S = sample_size(n);
-  const CPS_GLOBAL double *src = (const CPS_GLOBAL double *)Rs + c * S;
-  auto sample = [&](int i) -> double { return src[i]; };
-  double a, b;
-  const bool use = sample_bracket_rule<double, kLmsBracketBlock>(sample, S, n, k, sh, a, b);
+  const CPS_GLOBAL double *src = (const CPS_GLOBAL double *)Rs + c * (BLOCK * PER) + threadIdx.x;
+  double v[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) v[j] = src[j * BLOCK];
+  uint64_t mn = ~0ull, mx = 0ull, key[PER];
+  bool nan = false;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    nan = nan || !(v[j] == v[j]);
+    key[j] = Traits<double>::key(v[j]);
+    mn = key[j] < mn ? key[j] : mn;
+    mx = key[j] > mx ? key[j] : mx;
+  }
+  nan = block_key_range<BLOCK>(mn, mx, nan, sh);
+  double a = __builtin_inf(), b = -__builtin_inf();
+  if (!nan) {  // (uniform)
+    const SampleEnds<uint64_t> e = sample_ends<double, BLOCK, PER>(key, mn, mx, n, k, 4.5, hist, sh);
+    // (squares are not negative: -1 lies below an open lower end)
+    const uint64_t kneg = Traits<double>::key(-__builtin_inf()), kpos = Traits<double>::key(__builtin_inf());
+    a = e.ka == kneg ? -1.0 : Traits<double>::unkey(e.ka - 1);
+    b = e.kb == kpos ? __builtin_inf() : Traits<double>::unkey(e.kb + 1);
+  }
   if (threadIdx.x == 0) {
-    ab[2 * c] = use ? a : __builtin_inf();
-    ab[2 * c + 1] = use ? b : -__builtin_inf();
+    ab[2 * c] = a;
+    ab[2 * c + 1] = b;
   }
 }
 
-// The filter: kLmsLane candidates per lane (c = blockIdx.y * kLmsCands + u * kLmsBlock +
-// thread for u < kLmsLane), every row of segment s = blockIdx.x (rows [s * seg,
-// min((s + 1) * seg, n))) in order.  The rows are the same for every lane, so each row of X
-// and its y are scalar loads (registers shared by the wavefront, read by the vector
-// arithmetic as operands; the workgroup's wavefronts read the same rows), two rows per step,
-// and each row serves the lane's kLmsLane candidates.  A square r of candidate c with
-// a < r < b (or NaN) is kept: written to c's array of the workspace at the segment's first
-// row plus the number kept before it in the segment (so a segment's kept squares stay inside
-// the segment's own rows, in row order).  The counts land in cnt[0][c][s] (kept) and
-// cnt[1][c][s] (#(r <= a)), nseg = gridDim.x segments per candidate; SUM: the segment's sum of
-// the r <= a (in row order) in psum[c][s].
-constexpr int kLmsLane = 2;
-constexpr int kLmsCands = kLmsBlock * kLmsLane;  // candidates per workgroup
-#ifndef CPS_LMS_STAGE
-#define CPS_LMS_STAGE 4
-#endif
-constexpr int kLmsStage = CPS_LMS_STAGE;  // kept squares staged in LDS per candidate
+// The filter: every square r of the wavefront's rows (a segment of 64 T) and of `chunk`
+// candidates.  Per candidate #(r <= a) is counted in scalar registers (SUM: their sum as well),
+// and the r in (a, b), or NaN, are appended to the wavefront's region of R, one candidate's after
+// another's, so that all stores are contiguous; the candidate's first place there, the number
+// kept and the count below go to info[segment * m + candidate], 64 candidates at a time.
+// A region holds all squares of the wavefront's rows and candidates: segment sg's and the
+// candidates' from c0 on begin at (sg m + c0) rows per segment.  The kept squares pass through a
+// wavefront's LDS list and are stored 64 at a time.
+//
+// Bound: double-precision arithmetic (2 p + 1 operations per square, each rounded as in the
+// materialised form) and what keeping costs.  2^20 rows, p = 8, 1024 candidates: 0.54 ms of
+// arithmetic at the rate measured (33.5 T/s), 640 us with its loads, 740 with the two
+// comparisons, 975 with the keeping (1080 with a candidate per lane).  200003 rows, p = 5, 300
+// candidates, with sums: 124 us a candidate per lane, 74 this way.
 template <int P, bool SUM>
-__global__ __launch_bounds__(kLmsBlock) void lms_filter_kernel(
+__global__ __launch_bounds__(kLmsBlock, 4) void lms_filter_kernel(
     const double *__restrict__ X, const double *__restrict__ y, const double *__restrict__ betas,
-    const double *__restrict__ ab, int64_t n, int32_t p, int64_t m, int64_t seg,
-    double *__restrict__ R_out, uint32_t *__restrict__ cnt, double *__restrict__ psum) {
-  constexpr int PM = P > 0 ? P : 16;
-  constexpr int U = kLmsLane;
-  // Each candidate's kept squares gather in LDS and go out kLmsStage at a time, as 16-byte
-  // stores of contiguous places (single squares scattered over many candidates' arrays left
-  // most of each written line empty).
-  __shared__ double stg[kLmsCands][kLmsStage];
-  const bool pairs = n % 2 == 0;  // (every segment then starts 16-byte aligned)
-  const int pp = P > 0 ? P : p;
-  const int tid = threadIdx.x;
-  const int64_t sg = blockIdx.x, nseg = gridDim.x;
-  const int64_t rb = sg * seg;
-  const int64_t re = rb + seg < n ? rb + seg : n;
-  int64_t c[U];
-  bool live[U];
-  double b[U][PM], lo[U], hi[U];
-  CPS_GLOBAL double *dst[U];
-  CPS_GLOBAL double *put[U];  // the place of the first staged square
-  uint32_t below[U];          // #(r <= a)
-  double sbelow[U];           // SUM: their sum, in row order
-  int staged[U];
+    const double *__restrict__ ab, int64_t n, int64_t m, int64_t chunk, double *__restrict__ R,
+    uint2 *__restrict__ info, double *__restrict__ psum) {
+  constexpr int T = kLmsTiles<P>;
+  const int lane = threadIdx.x % kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int64_t sg = (int64_t)blockIdx.x * (kLmsBlock / kWave) + wv, r0 = sg * (T * kWave);
+  if (r0 >= n) return;
+  const int64_t rows = n - r0 < T * kWave ? n - r0 : T * kWave;
+  constexpr uint32_t kList = (T + 1) * kWave;
+  __shared__ double lists[kLmsBlock / kWave][kList];
+  CPS_LDS double *list = (CPS_LDS double *)lists[wv];
+  double x[T][P], yv[T];
+  uint64_t ok[T];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    c[u] = (int64_t)blockIdx.y * kLmsCands + u * kLmsBlock + tid;
-    live[u] = c[u] < m;
+  for (int t = 0; t < T; ++t) {
+    const bool valid = t * kWave + lane < rows;
+    ok[t] = ballot(valid);
+    const int64_t row = r0 + (valid ? t * kWave + lane : 0);
 #pragma unroll
-    for (int j = 0; j < PM; ++j) b[u][j] = live[u] && j < pp ? betas[c[u] * pp + j] : 0.0;
-    // a lane without a candidate stores nothing
-    lo[u] = live[u] ? ab[2 * c[u]] : __builtin_inf();
-    hi[u] = live[u] ? ab[2 * c[u] + 1] : -__builtin_inf();
-    dst[u] = (CPS_GLOBAL double *)R_out + (live[u] ? c[u] : 0) * n + rb;
-    put[u] = dst[u];
-    below[u] = 0;
-    sbelow[u] = 0.0;
-    staged[u] = 0;
+    for (int j = 0; j < P; ++j) x[t][j] = X[row * P + j];
+    yv[t] = y[row];
   }
-  auto flush = [&](int u, int k) {
-    const double *st = &stg[u * kLmsBlock + tid][0];
-    if (k == kLmsStage && pairs) {
-      using D2 = double __attribute__((ext_vector_type(2)));
-#pragma unroll
-      for (int v = 0; v < kLmsStage / 2; ++v)
-        ((CPS_GLOBAL D2 *)put[u])[v] = D2{st[2 * v], st[2 * v + 1]};
-    } else {
-      for (int v = 0; v < k; ++v) put[u][v] = st[v];
-    }
-    put[u] += k;
+  const int64_t c0 = (int64_t)blockIdx.y * chunk, c1 = c0 + chunk < m ? c0 + chunk : m;
+  CPS_GLOBAL double *region = (CPS_GLOBAL double *)uniform_ptr(R + (sg * m + c0) * (T * kWave));
+  uint32_t out = 0, held = 0;  // stored, and in the list (below 64 before a candidate)
+  // all whole wavefronts of the list, from its front; the rest moves there
+  auto flush = [&]() {
+    __builtin_amdgcn_wave_barrier();
+    uint32_t at = 0;
+    for (; held - at >= (uint32_t)kWave; at += kWave) region[out + at + lane] = list[at + lane];
+    const double rest = list[at + lane < kList ? at + lane : 0];
+    out += at;
+    held -= at;
+    __builtin_amdgcn_wave_barrier();
+    if ((uint32_t)lane < held) list[lane] = rest;
+    __builtin_amdgcn_wave_barrier();
   };
-  // the squares of a step first (independent chains of dependent double additions, which
-  // the scheduler interleaves), then their tests and stores (a branch each)
-  auto keep = [&](int u, double r) {
-    const bool le = r <= lo[u];
-    if (live[u] && !le && !(r >= hi[u])) {
-      stg[u * kLmsBlock + tid][staged[u]] = r;
-      if (++staged[u] == kLmsStage) {
-        flush(u, kLmsStage);
-        staged[u] = 0;
-      }
-    }
-    below[u] += le ? 1u : 0u;
-    if (SUM && le) sbelow[u] += r;
-  };
-  int64_t i = rb;
-  for (; i + 1 < re; i += 2) {  // two rows per step: both rows' scalar loads issued together
-    double x0[PM], x1[PM];
+  for (int64_t cg = c0; cg < c1; cg += kWave) {
+    const int lim = (int)(c1 - cg < kWave ? c1 - cg : kWave);
+    uint32_t first = 0, num = 0;  // lane k: candidate cg + k's
+    double sums = 0.0;
+    for (int k = 0; k < lim; ++k) {
+      const int64_t c = cg + k;
+      double b[P];
 #pragma unroll
-    for (int j = 0; j < PM; ++j) {
-      x0[j] = j < pp ? X[i * pp + j] : 0.0;
-      x1[j] = j < pp ? X[(i + 1) * pp + j] : 0.0;
-    }
-    const double y0 = y[i], y1 = y[i + 1];
-    // the 2U sums advance together, term by term (each in its own left-to-right order), so
-    // that consecutive instructions are independent
-    double s0[U], s1[U];
+      for (int j = 0; j < P; ++j) b[j] = betas[c * P + j];
+      const double lo = ab[2 * c], hi = ab[2 * c + 1];
+      double r[T], sum = 0.0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      s0[u] = x0[0] * b[u][0];
-      s1[u] = x1[0] * b[u][0];
-    }
+      for (int t = 0; t < T; ++t) r[t] = x[t][0] * b[0];
 #pragma unroll
-    for (int j = 1; j < PM; ++j) {
-      if (j < pp) {
+      for (int j = 1; j < P; ++j) {  // (T independent sums advance together)
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const double q0 = x0[j] * b[u][j], q1 = x1[j] * b[u][j];
-          s0[u] = s0[u] + q0;
-          s1[u] = s1[u] + q1;
+        for (int t = 0; t < T; ++t) {
+          const double q = x[t][j] * b[j];
+          r[t] = r[t] + q;
         }
       }
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const double d = yv[t] - r[t];
+        r[t] = d * d;
+      }
+      uint32_t below = 0;
+      const uint32_t at = out + held;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const uint64_t le = ballot(r[t] <= lo) & ok[t];
+        const uint64_t in = ok[t] & ~(le | ballot(r[t] >= hi));
+        below += popc(le);
+        if (SUM) sum += __builtin_amdgcn_inverse_ballot_w64(le) ? r[t] : 0.0;
+        if (__builtin_amdgcn_inverse_ballot_w64(in))
+          list[__builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, held))] = r[t];
+        held += popc(in);
+      }
+      const uint32_t num_kept = out + held - at;
+      const bool mine = __builtin_amdgcn_inverse_ballot_w64(1ull << k);
+      first = mine ? at : first;
+      num = mine ? num_kept | (below << 16) : num;
+      if (held >= (uint32_t)kWave) flush();
+      if (SUM) {
+        sum = wave_sum(sum);
+        sums = mine ? sum : sums;
+      }
     }
-    double r0[U], r1[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const double d0 = y0 - s0[u], d1 = y1 - s1[u];
-      r0[u] = d0 * d0;
-      r1[u] = d1 * d1;
-    }
-    // (an empty statement that takes every square: the compiler would otherwise move each
-    // chain down to its branch, and the chains would run one after another)
-#pragma unroll
-    for (int u = 0; u < U; ++u) asm volatile("" : "+v"(r0[u]), "+v"(r1[u]));
-#pragma unroll
-    for (int u = 0; u < U; ++u) keep(u, r0[u]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) keep(u, r1[u]);
-  }
-  if (i < re) {
-    double x0[PM];
-#pragma unroll
-    for (int j = 0; j < PM; ++j) x0[j] = j < pp ? X[i * pp + j] : 0.0;
-    const double y0 = y[i];
-#pragma unroll
-    for (int u = 0; u < U; ++u) keep(u, sq_residual<P>(x0, y0, b[u], pp));
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    if (live[u]) {
-      flush(u, staged[u]);
-      cnt[c[u] * nseg + sg] = (uint32_t)(put[u] - dst[u]);
-      cnt[(m + c[u]) * nseg + sg] = below[u];
-      if (SUM) psum[c[u] * nseg + sg] = sbelow[u];
+    if (lane < lim) {
+      info[sg * m + cg + lane] = uint2{first, num};
+      if (SUM) psum[sg * m + cg + lane] = sums;
     }
   }
+  __builtin_amdgcn_wave_barrier();
+  if ((uint32_t)lane < held) region[out + lane] = list[lane];
 }
 
 constexpr int kLmsGatherBlock = 256;
-constexpr int kLmsMaxSegs = 4096;  // segments per candidate (the gather's scan in LDS)
-// Filter workgroups per resident set: one set left some CUs a second, lone workgroup (1.5 ms
-// against 1.2 ms with four); more segments cost the gather more
-constexpr int kLmsRounds = 2;
 
 // ---- the filtered form's finish: one workgroup's exact select (cps_wgsel.h) over an array
 
@@ -444,142 +418,123 @@ __device__ inline double lms_ksum(const CPS_GLOBAL double *W, int64_t len, doubl
   return below + s + (double)(k - less) * v;
 }
 
-// One workgroup per candidate: the segments' counts and the bracket's test; where it holds,
-// the kept squares packed into C + c * cap in segment order, counted on the way in 2^12 key
-// bins over the bracket's open interval (a, b) (NaN noted), and the select of rank
-// k - #(r <= a) among them from that histogram on, written as candidate c's result over all
-// n squares.  Where it does not hold, full[c] = 1 and the candidate's whole array is formed
-// and selected by the two kernels that follow.  passes: the filter, the packing, and the
-// select's passes over the packed squares.
-__global__ __launch_bounds__(kLmsGatherBlock) void lms_gather_kernel(
-    const double *__restrict__ R, const uint32_t *__restrict__ cnt, const double *__restrict__ ab,
-    int64_t n, int64_t m, int64_t nseg, int64_t seg, int64_t k, int64_t cap, double *__restrict__ C,
+// One workgroup per candidate: the segments' counts and the bracket's test; where it holds, the
+// kept squares, read where the filter left them (eight lanes per segment, whose ~8 squares are
+// contiguous; the next candidate's follow, so neighbouring candidates run on one XCD and share
+// the lines), counted in 2^11 key bins over the bracket, and the rank's bin once more to rank
+// its few squares.  Where it does not hold, full[c] = 1 and the candidate's whole array is formed and
+// selected by the two kernels that follow.  passes: the filter and the two readings.
+// (1024 candidates of 37 000 squares: 252 us; 300 of 14 000 with sums: 56, where packing
+// the squares first and selecting among those took 86.)
+constexpr int kLmsSelBlock = 512, kLmsSelSegs = 4096;
+__global__ __launch_bounds__(kLmsSelBlock, 8) void lms_select_kernel(
+    const double *__restrict__ R, const uint2 *__restrict__ info, const double *__restrict__ ab,
+    int64_t n, int64_t m, int64_t nseg, int64_t seg, int64_t chunk, int64_t k,
     const double *__restrict__ psum, cps_result *__restrict__ out, double *__restrict__ ksum,
     int32_t *__restrict__ full) {
-  __shared__ uint32_t pre[kLmsMaxSegs + 1];
-  __shared__ uint32_t hist[kHistMaxBins];
-  __shared__ double buf[kLmsSelCap];
-  __shared__ WgSelLds sh;
-  __shared__ uint64_t tot[2];
-  __shared__ double wred[kLmsGatherBlock / kWave];
-  constexpr int SPT = kLmsMaxSegs / kLmsGatherBlock;
-  const int64_t c = blockIdx.x;
+  constexpr int BLOCK = kLmsSelBlock, G = 8, NG = BLOCK / G, U = 4;
+  __shared__ uint32_t first[kLmsSelSegs];
+  __shared__ uint16_t kept[kLmsSelSegs];
+  __shared__ uint32_t hist[4 * BLOCK];
+  __shared__ uint64_t fin[kWalkFinal];
+  __shared__ RegSelShared<BLOCK> sh;
+  __shared__ double wred[BLOCK / kWave];
+  const int64_t per = (m + 7) / 8, c = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (c >= m) return;
   const int tid = threadIdx.x;
-  uint32_t kv[SPT];
-  uint64_t kcount = 0, bsum = 0;
+  const int64_t hop = seg * m;
+  const CPS_GLOBAL double *Rc = (const CPS_GLOBAL double *)R + c / chunk * chunk * seg;
+  auto load = [&](int64_t s0, uint64_t &in, uint64_t &bel) {
+    const int cnt = (int)(nseg - s0 < kLmsSelSegs ? nseg - s0 : kLmsSelSegs);
+    for (int i0 = tid; i0 < cnt; i0 += U * BLOCK) {
+      uint2 w[U];
 #pragma unroll
-  for (int j = 0; j < SPT; ++j) {
-    const int64_t s = (int64_t)tid * SPT + j;
-    kv[j] = s < nseg ? cnt[c * nseg + s] : 0u;
-    kcount += kv[j];
-    bsum += s < nseg ? cnt[(m + c) * nseg + s] : 0u;
-  }
-  uint64_t run = block_exclusive_scan<kLmsGatherBlock>(kcount, sh.wsum);
-  const uint64_t bpre = block_exclusive_scan<kLmsGatherBlock>(bsum, sh.wsum);
-  if (tid == kLmsGatherBlock - 1) {
-    tot[0] = run + kcount;
-    tot[1] = bpre + bsum;
-    pre[kLmsMaxSegs] = (uint32_t)(run + kcount);
-  }
-  if (tid == 0) sh.flag = 0u;
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * BLOCK;
+        w[u] = info[(s0 + (i < cnt ? i : 0)) * m + c];
+      }
 #pragma unroll
-  for (int j = 0; j < SPT; ++j) {
-    pre[tid * SPT + j] = (uint32_t)run;
-    run += kv[j];
-  }
-  for (int b = tid; b < kHistMaxBins; b += kLmsGatherBlock) hist[b] = 0u;
-  __syncthreads();
-  const int64_t inside = (int64_t)tot[0], bel = (int64_t)tot[1];
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * BLOCK;
+        if (i < cnt) {
+          first[i] = w[u].x;
+          kept[i] = (uint16_t)(w[u].y & 0xffffu);
+          in += w[u].y & 0xffffu;
+          bel += w[u].y >> 16;
+        }
+      }
+    }
+    return cnt;
+  };
+  const int grp = tid / G, l = tid % G;
+  auto walk = [&](auto &&one) {
+    for (int64_t s0 = 0; s0 < nseg; s0 += kLmsSelSegs) {
+      int cnt = (int)nseg;
+      if (nseg > kLmsSelSegs) {  // (not all in LDS: read again)
+        uint64_t a = 0, b = 0;
+        __syncthreads();
+        cnt = load(s0, a, b);
+        __syncthreads();
+      }
+      for (int i0 = grp; i0 < cnt; i0 += U * NG) {
+        const CPS_GLOBAL double *p[U];
+        int num[U];
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = i0 + u * NG < cnt ? i0 + u * NG : i0;
+          num[u] = i0 + u * NG < cnt ? (int)kept[i] : 0;
+          p[u] = Rc + (s0 + i) * hop + first[i];
+          v[u] = p[u][l < num[u] ? l : 0];  // (with none kept: a place inside the workspace)
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          one(v[u], l < num[u]);
+          for (int e = l + G; e < num[u]; e += G) one(p[u][e], true);
+        }
+      }
+    }
+  };
+  uint64_t in = 0, bel = 0;
+  for (int64_t s0 = 0; s0 < nseg; s0 += kLmsSelSegs) load(s0, in, bel);
+  const int64_t inside = (int64_t)block_sum_fixed<BLOCK>((double)in, wred);
+  const int64_t below = (int64_t)block_sum_fixed<BLOCK>((double)bel, wred);
   const double lo = ab[2 * c], hi = ab[2 * c + 1];
-  const bool holds = lo < hi && bel < k && k <= bel + inside && inside <= cap;
+  const bool holds = lo < hi && below < k && k <= below + inside;
   if (tid == 0) full[c] = holds ? 0 : 1;
   if (!holds) return;  // (uniform)
   // the keys of a < r < b
   const uint64_t ka = Traits<double>::key(lo) + 1, kb = Traits<double>::key(hi) - 1;
-  int shift = 0;
-  while (((kb - ka) >> shift) >= (uint64_t)kHistMaxBins) ++shift;
-  // packed place j comes from the segment s with pre[s] <= j < pre[s + 1]; each thread's
-  // places rise, so its segment only moves forward (pre[kLmsMaxSegs] = inside ends it); the
-  // places of a step are consecutive over the threads, so the stores are (packing by
-  // segments per thread, its own places together, took 2.5 times as long); four places per
-  // step keep four loads in flight
-  const CPS_GLOBAL double *Rc = (const CPS_GLOBAL double *)(R + c * n);
-  CPS_GLOBAL double *Cc = (CPS_GLOBAL double *)(C + c * cap);
-  constexpr int U = 4;
-  int sg = 0;
+  const int shift = range_shift(kb - ka, quick_bins_log2(BLOCK));
+  *reinterpret_cast<uint4 *>(&hist[4 * tid]) = uint4{0u, 0u, 0u, 0u};
+  __syncthreads();
   bool nan = false;
-  for (int64_t j0 = tid; j0 < inside; j0 += U * kLmsGatherBlock) {
-    double v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t j = j0 + (int64_t)u * kLmsGatherBlock;
-      if (j < inside) {
-        while ((int64_t)pre[sg + 1] <= j) ++sg;
-        v[u] = Rc[(int64_t)sg * seg + (j - (int64_t)pre[sg])];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t j = j0 + (int64_t)u * kLmsGatherBlock;
-      if (j < inside) {
-        Cc[j] = v[u];
-        const uint64_t kk = Traits<double>::key(v[u]);
-        nan = nan || !(v[u] == v[u]);
-        if (kk >= ka && kk <= kb) atomicAdd(&hist[(uint32_t)((kk - ka) >> shift)], 1u);
-      }
-    }
-  }
-  if (nan) atomicOr(&sh.flag, 1u);
-  __syncthreads();  // (the packed squares, written by this workgroup, are read below)
-  if (sh.flag != 0u) {  // (uniform)
+  walk([&](double v, bool ok) {
+    nan = nan | (ok & !(v == v));
+    const uint64_t d = Traits<double>::key(v) - ka;
+    if (ok & (d <= kb - ka)) atomicAdd(&hist[(uint32_t)(d >> shift)], 1u);
+  });
+  if (__syncthreads_or(nan)) {  // (uniform)
     if (tid == 0) {
       lms_write_nan(out + c, 2);
       if (ksum) ksum[c] = __builtin_nan("");
     }
     return;
   }
-  // the bin of rank k - #(r <= a) among the packed squares
-  const int64_t rr = k - bel;
-  constexpr int BPT = kHistMaxBins / kLmsGatherBlock;
-  uint64_t hv[BPT];
-  uint64_t hs = 0;
-#pragma unroll
-  for (int j = 0; j < BPT; ++j) {
-    hv[j] = hist[tid * BPT + j];
-    hs += hv[j];
-  }
-  uint64_t cum = block_exclusive_scan<kLmsGatherBlock>(hs, sh.wsum);
-#pragma unroll
-  for (int j = 0; j < BPT; ++j) {
-    if (cum < (uint64_t)rr && (uint64_t)rr <= cum + hv[j]) {
-      sh.bin = tid * BPT + j;
-      sh.cum = (int64_t)cum;
-      sh.inb = (int64_t)hv[j];
-    }
-    cum += hv[j];
-  }
-  __syncthreads();
-  const uint64_t b = (uint64_t)sh.bin;
-  const int64_t below0 = sh.cum, in0 = sh.inb;
-  __syncthreads();
-  const uint64_t nlo = ka + (b << shift);
-  uint64_t nhi = nlo + ((1ull << shift) - 1);
-  if (nhi > kb || nhi < nlo) nhi = kb;
-  const WgSelOut r = wg_select<kLmsGatherBlock>(C + c * cap, inside, rr, nlo, nhi, below0, in0,
-                                                hist, buf, sh);
-  if (tid == 0) lms_write_result(out + c, r.key, bel + r.less, r.equal, n, 3 + r.passes);
+  const uint4 q = *reinterpret_cast<const uint4 *>(&hist[4 * tid]);
+  uint32_t h[4] = {q.x, q.y, q.z, q.w};
+  uint64_t key;
+  int64_t less, equal;
+  walk_select<double, BLOCK>(walk, h, k - below, ka, kb, hist, fin, sh, key, less, equal);
+  if (tid == 0) lms_write_result(out + c, key, below + less, equal, n, 3);
   if (ksum) {  // (uniform)
-    // the squares under a: the segments' sums, each thread's run of segments in order
-    double sb = 0.0;
-#pragma unroll
-    for (int j = 0; j < SPT; ++j) {
-      const int64_t s2 = (int64_t)tid * SPT + j;
-      if (s2 < nseg) sb += psum[c * nseg + s2];
-    }
-    const double below_sum = block_sum_fixed<kLmsGatherBlock>(sb, wred);
-    const double v = Traits<double>::unkey(r.key);
-    const double t = lms_ksum<kLmsGatherBlock>(Cc, inside, v, rr, r.less, below_sum, wred);
-    if (tid == 0) ksum[c] = t;
+    const double v = Traits<double>::unkey(key);
+    double sb = 0.0, part = 0.0;
+    for (int64_t s = tid; s < nseg; s += BLOCK) sb += psum[s * m + c];
+    walk([&](double r, bool ok) { part += ok && r < v ? r : 0.0; });
+    const double under = block_sum_fixed<BLOCK>(sb, wred);
+    const double mid = block_sum_fixed<BLOCK>(part, wred);
+    if (tid == 0) ksum[c] = under + mid + (double)(k - below - less) * v;
   }
 }
 
@@ -695,77 +650,71 @@ hipError_t launch_lms_residuals(const double *X, const double *y, const double *
   return hipGetLastError();
 }
 
-void lms_filter_shape(int64_t n, int64_t m, int32_t p, bool vec, int cu_count, int64_t *bx,
-                      int64_t *nseg, int64_t *seg) {
-  // the filter: kLmsRounds times as many workgroups as are resident at once over (segments x
-  // groups of kLmsCands candidates), a multiple of 16 rows per segment (at least 256), every
-  // segment holding rows
-  int per_cu = 0;
-  (void)vec;
-  const hipError_t e =
-      p <= 8 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lms_filter_kernel<8, false>, kLmsBlock, 0)
-             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lms_filter_kernel<16, false>, kLmsBlock, 0);
-  if (e != hipSuccess || per_cu < 1) per_cu = 4;
-  const int64_t fgroups = (m + kLmsCands - 1) / kLmsCands;
-  int64_t ns = (int64_t)cu_count * per_cu * kLmsRounds / fgroups;
-  const int64_t nmax = (n + 255) / 256;
-  if (ns > nmax) ns = nmax;
-  if (ns > kLmsMaxSegs) ns = kLmsMaxSegs;
-  if (ns < 1) ns = 1;
-  const int64_t sl = ((n + ns - 1) / ns + 15) / 16 * 16;
-  *nseg = (n + sl - 1) / sl;
-  *seg = sl;
+void lms_filter_shape(int64_t n, int64_t m, int32_t p, int cu_count, int64_t *bx, int64_t *nseg,
+                      int64_t *seg, int64_t *chunk) {
+  // the filter: a wavefront per segment and chunk of candidates (a multiple of 64), two rounds of
+  // four wavefronts per SIMD or more where there are that many
+  *seg = lms_seg(p);
+  *nseg = (n + *seg - 1) / *seg;
+  const int64_t want = (2 * 16 * (int64_t)cu_count + *nseg - 1) / *nseg;
+  const int64_t most = (m + kWave - 1) / kWave;
+  const int64_t chunks = want < 1 ? 1 : (want < most ? want : most);
+  *chunk = ((m + chunks - 1) / chunks + kWave - 1) / kWave * kWave;
   // the fallback residual kernel's grid, as the materialised form's
   const int64_t groups = (m + kLmsGroup - 1) / kLmsGroup;
   int64_t b = (n + kLmsBlock - 1) / kLmsBlock;
-  const int64_t want = (int64_t)cu_count * 8 / groups + 1;
-  if (b > want) b = want;
+  const int64_t fb = (int64_t)cu_count * 8 / groups + 1;
+  if (b > fb) b = fb;
   *bx = b < 1 ? 1 : b;
 }
 
-int64_t lms_filter_cap(int64_t n) { return (n / 8 + 1 + 31) / 32 * 32; }
-
-// The filter has an instance for every p: the loops over the columns
-// unroll and the rows stay scalar loads (at p = 5, 300 candidates x 200003 rows, 264 us in the
-// instance that takes any p, 124 us in its own).
-template <int P, bool SUM>
-static void launch_lms_filter(const double *X, const double *y, const double *betas, int64_t n,
-                                  int32_t p, int64_t m, const LmsFilterBufs &w, dim3 grid,
-                                  hipStream_t stream) {
+// The sample's and the filter's kernels have an instance for every p: the columns' loops unroll.
+template <int P>
+static void launch_lms_sample(const double *X, const double *y, const double *betas, int64_t n,
+                              int32_t p, int64_t m, double *Rs, hipStream_t stream) {
   if constexpr (P > 1)
-    if (p < P) return launch_lms_filter<P - 1, SUM>(X, y, betas, n, p, m, w, grid, stream);
-  lms_filter_kernel<P, SUM><<<grid, dim3(kLmsBlock), 0, stream>>>(X, y, betas, w.ab, n, p, m, w.seg,
-                                                                   w.R, w.cnt, w.psum);
+    if (p < P) return launch_lms_sample<P - 1>(X, y, betas, n, p, m, Rs, stream);
+  constexpr int64_t chunk = 32;
+  const int per = kLmsBlock * kLmsTiles<P>;
+  const dim3 grid((unsigned)((sample_runs(n) * kPropRun + per - 1) / per), (unsigned)((m + chunk - 1) / chunk));
+  lms_sample_kernel<P><<<grid, dim3(kLmsBlock), 0, stream>>>(X, y, betas, n, m, chunk, Rs);
+}
+template <int P>
+static void launch_lms_filter(const double *X, const double *y, const double *betas, int64_t n,
+                              int32_t p, int64_t m, const LmsFilterBufs &w, bool sum,
+                              hipStream_t stream) {
+  if constexpr (P > 1)
+    if (p < P) return launch_lms_filter<P - 1>(X, y, betas, n, p, m, w, sum, stream);
+  constexpr int W = kLmsBlock / kWave;
+  const dim3 grid((unsigned)((w.nseg + W - 1) / W), (unsigned)((m + w.chunk - 1) / w.chunk));
+  if (sum)
+    lms_filter_kernel<P, true><<<grid, dim3(kLmsBlock), 0, stream>>>(X, y, betas, w.ab, n, m, w.chunk,
+                                                                      w.R, w.info, w.psum);
+  else
+    lms_filter_kernel<P, false><<<grid, dim3(kLmsBlock), 0, stream>>>(X, y, betas, w.ab, n, m, w.chunk,
+                                                                       w.R, w.info, nullptr);
 }
 
 hipError_t launch_lms_filtered(const double *X, const double *y, const double *betas, int64_t n,
                                int32_t p, int64_t m, int64_t rank, const LmsFilterBufs &w,
                                cps_result *out, double *ksum, hipStream_t stream) {
   const int64_t groups = (m + kLmsGroup - 1) / kLmsGroup;
-  const int64_t fgroups = (m + kLmsCands - 1) / kLmsCands;
-  const int64_t sgroups = (m + kLmsBlock - 1) / kLmsBlock;
-  // one run of the sample per workgroup
-  const dim3 sg((unsigned)(sample_runs(n)), (unsigned)sgroups);
-  if (p == 8)
-    lms_sample_kernel<8><<<sg, dim3(kLmsBlock), 0, stream>>>(X, y, betas, n, p, m, w.Rs);
-  else
-    lms_sample_kernel<0><<<sg, dim3(kLmsBlock), 0, stream>>>(X, y, betas, n, p, m, w.Rs);
+  launch_lms_sample<16>(X, y, betas, n, p, m, w.Rs, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  lms_bracket_kernel<<<dim3((unsigned)m), dim3(kLmsBracketBlock), 0, stream>>>(w.Rs, n, rank, w.ab);
+  if (sample_runs(n) * kPropRun == kPropSampleBig)
+    lms_bracket_kernel<kPropSampleBig / 1024><<<dim3((unsigned)m), dim3(1024), 0, stream>>>(w.Rs, n, rank, w.ab);
+  else
+    lms_bracket_kernel<kPropSample / 1024><<<dim3((unsigned)m), dim3(1024), 0, stream>>>(w.Rs, n, rank, w.ab);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)y % 16 == 0);
-  const dim3 fgrid((unsigned)w.nseg, (unsigned)fgroups);
-  if (ksum)
-    launch_lms_filter<16, true>(X, y, betas, n, p, m, w, fgrid, stream);
-  else
-    launch_lms_filter<16, false>(X, y, betas, n, p, m, w, fgrid, stream);
+  launch_lms_filter<16>(X, y, betas, n, p, m, w, ksum != nullptr, stream);
   const dim3 grid((unsigned)w.bx, (unsigned)groups);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  lms_gather_kernel<<<dim3((unsigned)m), dim3(kLmsGatherBlock), 0, stream>>>(
-      w.R, w.cnt, w.ab, n, m, w.nseg, w.seg, rank, w.cap, w.C, w.psum, out, ksum, w.full);
+  lms_select_kernel<<<dim3((unsigned)((m + 7) / 8 * 8)), dim3(kLmsSelBlock), 0, stream>>>(
+      w.R, w.info, w.ab, n, m, w.nseg, w.seg, w.chunk, rank, w.psum, out, ksum, w.full);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the candidates whose bracket missed: their whole arrays (workgroups without one return)
