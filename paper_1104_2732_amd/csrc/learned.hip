@@ -599,16 +599,23 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_few_kernel(const float *__
     sh.W2[q / kHid * kHS + q % kHid] = w2[r];
   }
   __syncthreads();
-  // ---- forward (a wavefront's own example: no workgroup barrier needed between layers)
-  float z1 = 0.0f, z2 = 0.0f;
+  // ---- forward (a wavefront's own example: no workgroup barrier needed between layers); each sum
+  // in four parts, which is shorter and rounds less than one chain
+  float z1, z2;
+  {
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int i = 0; i < kIn; ++i) z1 = z1 + sh.W1[j * kIn + i] * sh.X[e][i];
-  z1 = z1 + b1;
+    for (int i = 0; i < kIn; ++i) s[i % 4] = s[i % 4] + sh.W1[j * kIn + i] * sh.X[e][i];
+    z1 = ((s[0] + s[1]) + (s[2] + s[3])) + b1;
+  }
   sh.H1[e][j] = relu(z1);
   __builtin_amdgcn_wave_barrier();
+  {
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int i = 0; i < kHid; ++i) z2 = z2 + sh.W2[j * kHS + i] * sh.H1[e][i];
-  z2 = z2 + b2;
+    for (int i = 0; i < kHid; ++i) s[i % 4] = s[i % 4] + sh.W2[j * kHS + i] * sh.H1[e][i];
+    z2 = ((s[0] + s[1]) + (s[2] + s[3])) + b2;
+  }
   const float h2 = relu(z2);
   sh.H2[e][j] = h2;
   // ---- the outputs (float products, summed in double), loss and its derivatives
@@ -630,9 +637,13 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_few_kernel(const float *__
   // ---- backward
   sh.D2[e][j] = z2 > 0.0f ? d0 * w30 + d1 * w31 : 0.0f;
   __builtin_amdgcn_wave_barrier();
-  float g = 0.0f;
+  float g;
+  {
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int i = 0; i < kHid; ++i) g = g + sh.D2[e][i] * sh.W2[i * kHS + j];
+    for (int i = 0; i < kHid; ++i) s[i % 4] = s[i % 4] + sh.D2[e][i] * sh.W2[i * kHS + j];
+    g = (s[0] + s[1]) + (s[2] + s[3]);
+  }
   sh.D1[e][j] = z1 > 0.0f ? g : 0.0f;
   __syncthreads();
   // ---- the examples' sums, in example order
@@ -664,23 +675,23 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_few_kernel(const float *__
 }
 
 // Their sum: 64 places per workgroup, each by 8 threads over an eighth of the workgroups in order,
-// then the eighths in order.
+// then the eighths in order, in double.
 __global__ __launch_bounds__(512) void mlp_reduce_few_kernel(const float *__restrict__ part, int nwg,
                                                              float *__restrict__ grad,
                                                              float *__restrict__ loss) {
   constexpr int NP = 64, NG = 8, U = 8;
-  __shared__ float sum[NG][NP];
+  __shared__ double sum[NG][NP];
   const int c = threadIdx.x % NP, g = threadIdx.x / NP;
   const int p = blockIdx.x * NP + c;
   const int w0 = (int)((int64_t)nwg * g / NG), w1 = (int)((int64_t)nwg * (g + 1) / NG);
   const float *src = part + (p <= kParams ? p : 0);
-  float s = 0.0f;
+  double s = 0.0;
   for (int w = w0; w < w1; w += U) {
     float v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = src[(int64_t)(w + u < w1 ? w + u : w0) * (kParams + 1)];
 #pragma unroll
-    for (int u = 0; u < U; ++u) s = w + u < w1 ? s + v[u] : s;
+    for (int u = 0; u < U; ++u) s += w + u < w1 ? (double)v[u] : 0.0;
   }
   sum[g][c] = s;
   __syncthreads();
@@ -688,8 +699,8 @@ __global__ __launch_bounds__(512) void mlp_reduce_few_kernel(const float *__rest
     s = sum[0][c];
 #pragma unroll
     for (int i = 1; i < NG; ++i) s = s + sum[i][c];
-    if (p < kParams) grad[p] = s;
-    else if (loss) *loss = s;
+    if (p < kParams) grad[p] = (float)s;
+    else if (loss) *loss = (float)s;
   }
 }
 
