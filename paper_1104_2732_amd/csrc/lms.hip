@@ -236,9 +236,9 @@ __global__ __launch_bounds__(1024) void lms_bracket_kernel(const double *__restr
   double a = __builtin_inf(), b = -__builtin_inf();
   if (!nan) {  // (uniform)
     const SampleEnds<uint64_t> e = sample_ends<double, BLOCK, PER>(key, mn, mx, n, k, 4.5, hist, sh);
-    // (squares are not negative: -1 lies below an open lower end)
-    const uint64_t kneg = Traits<double>::key(-__builtin_inf()), kpos = Traits<double>::key(__builtin_inf());
-    a = e.ka == kneg ? -1.0 : Traits<double>::unkey(e.ka - 1);
+    // (squares are not negative: -1 lies below an open lower end, and below 0)
+    const uint64_t kpos = Traits<double>::key(__builtin_inf());
+    a = e.ka <= Traits<double>::key(0.0) ? -1.0 : Traits<double>::unkey(e.ka - 1);
     b = e.kb == kpos ? __builtin_inf() : Traits<double>::unkey(e.kb + 1);
   }
   if (threadIdx.x == 0) {
