@@ -269,11 +269,14 @@ __device__ __forceinline__ __bf16 bf16_part(float v, bool lo) {
 }
 using BF8 = __bf16 __attribute__((ext_vector_type(8)));
 
-// The distances of the sampled points (runs of kPropRun at sample_stride apart), one query
-// per lane, the points as scalar loads; one run per workgroup along x.  The first workgroup
+// The distances of the sampled points (runs of kPropRun at sample_stride apart) to
+// Ds[query * S + i]: kSmpTiles points per lane, the queries of a chunk as scalar loads, so that a
+// store is a whole line of one query's array (a query per lane, its run as 16-byte stores of one
+// 64-byte line: 34 us for 1024 queries x 16384 samples, this 18).  The first workgroup
 // also leaves the mean of 64 points spread over P in centre[0, dim) (a coordinate whose mean
 // is not an ordinary number: 0), which the screen takes as its origin; any origin gives the
 // same results.
+constexpr int kSmpTiles = 4, kSmpChunk = 32;
 template <int D>
 __global__ __launch_bounds__(kKnnBlock) void knn_sample_kernel(
     const float *__restrict__ P, const float *__restrict__ Q, int64_t n, int32_t dim, int64_t nq,
@@ -287,31 +290,26 @@ __global__ __launch_bounds__(kKnnBlock) void knn_sample_kernel(
       if (threadIdx.x == 0) centre[j] = fabs(s) < 1e18 ? (float)s : 0.0f;
     }
   }
-  const int64_t q = (int64_t)blockIdx.y * kKnnBlock + threadIdx.x;
-  const bool live = q < nq;
-  float qv[DM];
-#pragma unroll
-  for (int j = 0; j < DM; ++j) qv[j] = live && j < dd ? Q[q * dd + j] : 0.0f;
   const int S = sample_size(n);
   const int64_t stride = sample_stride(n, S);
-  const int run = blockIdx.x;
-  using F4 = float __attribute__((ext_vector_type(4)));
-  static_assert(kPropRun % 4 == 0, "whole vectors per run");
-  // (a lane's run goes out as 16-byte stores of one 64-byte line of its query's array: as
-  // sixteen single stores 1024 queries x 16384 samples took 58 us)
-  CPS_GLOBAL F4 *dst = (CPS_GLOBAL F4 *)(Ds + (live ? q : 0) * S + run * kPropRun);
+  const int i0 = (int)blockIdx.x * kKnnBlock * kSmpTiles + threadIdx.x;  // (S is a multiple)
+  float row[kSmpTiles][DM];
 #pragma unroll
-  for (int r = 0; r < kPropRun; r += 4) {
-    F4 d;
+  for (int t = 0; t < kSmpTiles; ++t) {
+    const int i = i0 + t * kKnnBlock;
+    const int64_t r = (int64_t)(i / kPropRun) * stride + i % kPropRun;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t i = (int64_t)run * stride + r + e;
-      float row[DM];
+    for (int j = 0; j < DM; ++j) row[t][j] = j < dd ? P[r * dd + j] : 0.0f;
+  }
+  const int64_t q0 = (int64_t)blockIdx.y * kSmpChunk, q1 = q0 + kSmpChunk < nq ? q0 + kSmpChunk : nq;
+  CPS_GLOBAL float *dst = (CPS_GLOBAL float *)Ds + q0 * S + i0;
+  for (int64_t q = q0; q < q1; ++q) {
+    float qv[DM];
 #pragma unroll
-      for (int j = 0; j < DM; ++j) row[j] = j < dd ? P[i * dd + j] : 0.0f;
-      d[e] = knn_dist_reg<D>(row, qv, dim);
-    }
-    if (live) dst[r / 4] = d;
+    for (int j = 0; j < DM; ++j) qv[j] = j < dd ? Q[q * dd + j] : 0.0f;
+#pragma unroll
+    for (int t = 0; t < kSmpTiles; ++t) dst[t * kKnnBlock] = knn_dist_reg<D>(row[t], qv, dim);
+    dst += S;
   }
 }
 
@@ -884,7 +882,9 @@ hipError_t launch_knn_filtered(const float *P, const float *f, const float *Q, i
                                int32_t dim, int64_t nq, int64_t k, const KnnFilterBufs &w,
                                cps_knn *out, hipStream_t stream) {
   const int64_t groups = (nq + kKnnBlock - 1) / kKnnBlock;
-  const dim3 sg((unsigned)sample_runs(n), (unsigned)groups);
+  static_assert(kPropSample % (kKnnBlock * kSmpTiles) == 0, "whole workgroups of samples");
+  const dim3 sg((unsigned)(sample_runs(n) * kPropRun / (kKnnBlock * kSmpTiles)),
+                (unsigned)((nq + kSmpChunk - 1) / kSmpChunk));
   if (dim == 8)
     knn_sample_kernel<8><<<sg, dim3(kKnnBlock), 0, stream>>>(P, Q, n, dim, nq, w.Ds, w.centre);
   else
