@@ -427,12 +427,13 @@ int lms_median_sq_residuals(cps_handle *h, const double *X_dev, const double *y_
  * CPS_LMS_FILTERED (n from 2^15 to 2^31 - 1): each candidate's sampled bracket (a, b) is
  *   taken from the squares of a fixed sample of rows (as the batched kernel samples an array
  *   of n elements), one kernel forms every r_i and keeps only those in (a, b) (and NaN),
- *   with #(r <= a), and the kept squares are packed and selected at rank k - #(r <= a).  A
- *   candidate whose bracket does not hold the median, or whose kept squares exceed n/8, gets
- *   its whole array written and selected as in the materialised form.  The workspace holds
- *   m * n + m * (n/8) doubles.  `passes` then counts the one pass that forms the residuals
- *   plus the selection's passes over the packed squares.
- * CPS_LMS_AUTO: the filtered form where n allows it, else the materialised one. */
+ *   with #(r <= a), and the kept squares are selected at rank k - #(r <= a) where they lie.  A
+ *   candidate whose bracket does not hold the median gets its whole array written and
+ *   selected as in the materialised form.  The workspace holds m * n doubles and an eighth of
+ *   a byte per square.  `passes` then counts the one pass that forms the residuals and the
+ *   two readings of the kept squares.
+ * CPS_LMS_AUTO: the filtered form from n = 2^14 on (knn_mean: 2^13), else the materialised
+ *   one. */
 enum cps_lms_form { CPS_LMS_AUTO = 0, CPS_LMS_MATERIALISED = 1, CPS_LMS_FILTERED = 2 };
 
 /* lms_median_sq_residuals with a choice of form (above).  Errors: as
@@ -480,8 +481,8 @@ int lts_trimmed_sq(cps_handle *h, const double *X_dev, const double *y_dev,
 
 /* lts_trimmed_sq with a choice of form (cps_lms_form; CPS_LMS_AUTO is lts_trimmed_sq).  In
  * the filtered form the bracket is taken for rank hk, the filter also sums the squares at or
- * below its lower end (per row segment, in row order; the segments' sums added in a fixed
- * order), and one more pass over the packed squares sums those below the selected value, so
+ * below its lower end (per row segment; the segments' sums added in a fixed
+ * order), and one more pass over the kept squares sums those below the selected value, so
  * F is formed in double precision in a fixed order.  Errors: as lts_trimmed_sq, and
  * CPS_EINVAL for a form outside cps_lms_form, or CPS_LMS_FILTERED with n outside
  * [2^15, 2^31). */
@@ -514,7 +515,7 @@ int knn_mean(cps_handle *h, const float *P_dev, const float *f_dev, const float 
              int32_t dim, int64_t nq, int64_t k, cps_knn *out_dev, void *stream);
 
 /* knn_mean with a choice of form (cps_lms_form; CPS_LMS_AUTO is knn_mean, which takes the
- * filtered form from n = 2^15 on).  Filtered: each query's sampled bracket (a, b) from the
+ * filtered form from n = 2^13 on).  Filtered: each query's sampled bracket (a, b) from the
  * distances of the points the batched kernel would sample, one pass over the points that
  * keeps the distances in (a, b) (and NaN) with their ordinates (at most 8128 per query),
  * counting d <= a and summing its ordinates; d_k by a radix select among the kept ones, the
