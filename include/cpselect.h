@@ -429,8 +429,8 @@ int lms_median_sq_residuals(cps_handle *h, const double *X_dev, const double *y_
  *   of n elements), one kernel forms every r_i and keeps only those in (a, b) (and NaN),
  *   with #(r <= a), and the kept squares are selected at rank k - #(r <= a) where they lie.  A
  *   candidate whose bracket does not hold the median gets its whole array written and
- *   selected as in the materialised form.  The workspace holds m * n doubles and an eighth of
- *   a byte per square.  `passes` then counts the one pass that forms the residuals and the
+ *   selected as in the materialised form.  The workspace holds m * n doubles and about one per
+ *   cent more.  `passes` then counts the one pass that forms the residuals and the
  *   two readings of the kept squares.
  * CPS_LMS_AUTO: the filtered form from n = 2^14 on (knn_mean: 2^13), else the materialised
  *   one. */

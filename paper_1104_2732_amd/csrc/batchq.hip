@@ -25,7 +25,8 @@
 // is the copies), 70 on samples and their ends, 42 on selects, 19 between items.  Comparing and
 // appending element by element instead of by vectors (RowFilter): 690 us.  With the key bins
 // counted by a walk over the kept elements instead of on the way: 580 and 355 us (the last
-// array's select alone 100 us).
+// array's select alone 100 us).  Many large float64 arrays gain least, as their copies are the
+// widest writes: 512 of 2^20 elements 952 us (general 958; with a sample of 8192 for 12288, 970).
 #include "batch_queue.h"
 #include "cps_quick.h"
 
@@ -36,21 +37,22 @@ constexpr int kBqWaves = kBqBlock / kWave;
 template <typename T> constexpr int kBqPer = sizeof(T) == 4 ? 32 : 16;  // keys per lane, small arrays
 template <typename T> constexpr int kBqSmall = kBqBlock * kBqPer<T>;
 constexpr int kBqSmpA = 8;                       // samples per lane: 4096 in all, or
-template <typename T> constexpr int kBqSmpB = sizeof(T) == 4 ? 32 : 16;  // 16384 (8192)
+template <typename T> constexpr int kBqSmpB = sizeof(T) == 4 ? 32 : 24;  // 16384 (12288)
 constexpr int kBqU = 4;                          // vectors per lane and tile
 constexpr size_t kBqListBytes = 49152;           // LDS for the inside elements
 constexpr int64_t kBqMaxN = (int64_t)1 << 31;    // larger arrays go to the general kernel
 constexpr double kBqDev = 4.5;  // deviations of the interval's ends: a miss in 10^5 arrays
 // Arrays from this many elements on are shared by workgroups: smaller ones keep their inside
 // elements in LDS.  The interval holds 3.6 % of the elements at most with float32's large sample
-// (5.0 % with float64's), 7.1 % with the small one: 9300 of 12288 places (3300 of 6144).
+// (4.1 % with float64's), 7.1 % with the small one: 9300 of 12288 places (2700 of 6144).
 template <typename T> constexpr int64_t kBqShare = (int64_t)1 << (sizeof(T) == 4 ? 18 : 16);
 
 template <typename T> CPS_HD inline bool bq_big_sample(int64_t n) { return n >= kBqShare<T> / 2; }
 template <typename T> CPS_HD inline bool bq_shared(int64_t n) { return n >= kBqShare<T> && n <= kBqMaxN; }
-// A shared array's region of the pool: room for an eighth of its elements (the interval holds
-// 5 %), then the key bins of each part.
-CPS_HD inline int64_t bq_room(int64_t n) { return (n / 8 + 63) / 64 * 64; }
+// A shared array's region of the pool: room for a sixteenth of its elements (the interval holds
+// 3.6 % of them, of float64 4.1 %, give or take 5 % of that), then the key bins of each part.
+// Arrays that find no region are left to the general kernel unread.
+CPS_HD inline int64_t bq_room(int64_t n) { return (n / 16 + 63) / 64 * 64; }
 constexpr int kBqBins = 4 * kBqBlock, kBqBinsLog2 = quick_bins_log2(kBqBlock);
 template <typename T> CPS_HD inline int64_t bq_region(int64_t n, uint32_t parts) {
   return bq_room(n) + (int64_t)parts * (int64_t)(kBqBins * sizeof(uint32_t) / sizeof(T));
@@ -169,7 +171,6 @@ __global__ __launch_bounds__(1024) void batchq_order_kernel(BatchqArgs<T> a, int
       if (bq_shared<T>(s.n)) {
         BatchqRec r = {};
         r.region = unit[i] != ~0u ? (int64_t)unit[i] * 64 : -1;
-        r.over = unit[i] != ~0u ? 0u : 1u;
         a.rec[i] = r;
       }
     }
@@ -311,6 +312,10 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
   constexpr uint32_t kSeg = (uint32_t)(kBqListBytes / sizeof(T) / kBqWaves);  // places per wavefront
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+  if (rec && rec->region < 0) {  // (uniform)
+    if (tid == 0 && part == 0) bq_redo<T>(a, jj);
+    return;
+  }
   SampleEnds<Key> e;
   const Span<T> sp = make_span(x, n);
   const bool num = bq_big_sample<T>(n) ? bq_ends<T, kBqSmpB<T>>(sp, n, k, sh, e)
@@ -321,9 +326,9 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
   }
   RowFilter<T> f(e, sh.rows[wv]);
   const int64_t region = rec ? rec->region : 0, room = bq_room(n);
-  CPS_GLOBAL T *z = (CPS_GLOBAL T *)(a.pool + (region < 0 ? 0 : region));
+  CPS_GLOBAL T *z = (CPS_GLOBAL T *)(a.pool + region);
   if (tid < 3) sh.count[tid] = 0ull;
-  if (tid == 0) sh.over = region < 0 ? 1u : 0u;  // (2: NaN)
+  if (tid == 0) sh.over = 0u;  // (1: no room; 2: NaN)
   *reinterpret_cast<uint4 *>(&sh.hist[4 * tid]) = uint4{0u, 0u, 0u, 0u};
   const int shift = range_shift((uint64_t)(e.ib - e.ia), kBqBinsLog2);
   __syncthreads();
@@ -336,7 +341,7 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
       at = __hip_atomic_fetch_add(&rec->cursor, (uint64_t)held, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int64_t off = (int64_t)__shfl(at, 0);
     __builtin_amdgcn_wave_barrier();
-    if (region >= 0 && off + held <= room) {
+    if (off + held <= room) {
       for (uint32_t i = lane; i < held; i += kWave) z[off + i] = sh.list[wv][i];
     } else if (lane == 0) {
       atomicOr(&sh.over, 1u);
@@ -432,8 +437,8 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
     h[3] = q.w;
   }
   if (rec) {
-    uint4 *bins = region < 0 ? nullptr : reinterpret_cast<uint4 *>(a.pool + region + room);
-    if (bins && parts > 1) {
+    uint4 *bins = reinterpret_cast<uint4 *>(a.pool + region + room);
+    if (parts > 1) {
       bins[(int64_t)part * kBqBlock + tid] = uint4{h[0], h[1], h[2], h[3]};
       __syncthreads();
     }
@@ -454,7 +459,7 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
     cb = (int64_t)load_relaxed(&rec->eb);
     inner = (int64_t)load_relaxed(&rec->cursor);
     over = load_relaxed(&rec->over);
-    if (bins && parts > 1) {
+    if (parts > 1) {
       h[0] = h[1] = h[2] = h[3] = 0u;
       for (uint32_t p = 0; p < parts; p += 8) {
         uint4 w[8];

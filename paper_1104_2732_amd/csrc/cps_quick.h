@@ -304,8 +304,8 @@ template <typename Key> struct SampleEnds {
 // only comparisons, scalar counts and one LDS write of the vectors that hold an inside element
 // (a tenth to a fifth of them); 64 of these at a time are taken apart element by element, by full
 // lanes.  Masks are combined as scalars: per-lane booleans cost two vector instructions each time
-// they become a mask.  (Element by element, each with its own branch, the loop took 105 cycles
-// per 64 elements and SIMD at 4 to 6 wavefronts, whatever the memory did.)
+// they become a mask.  (Element by element, each with its own branch: 2^24 float32 45 us a call,
+// this way 43; the default batch of 4096 arrays 690 us, this way 620.)
 template <typename T> struct RowFilter {
   using Vec = typename Traits<T>::Vec;
   static constexpr int V = Traits<T>::kVec;

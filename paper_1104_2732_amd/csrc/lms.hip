@@ -362,9 +362,8 @@ constexpr int kLmsGatherBlock = 256;
 
 // ---- the filtered form's finish: one workgroup's exact select (cps_wgsel.h) over an array
 
-// elements a narrowed key range may hold to finish in LDS (992: the gather kernel then fits
-// four workgroups per CU, so 1024 candidates run in one round; 1024 left a second round of
-// 256 on a third of the chip)
+// elements a narrowed key range may hold to finish in LDS (a candidate selected over all its n
+// squares)
 constexpr int kLmsSelCap = 992;
 using WgSelLds = WgSelShared<kLmsGatherBlock>;
 
