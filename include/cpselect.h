@@ -312,9 +312,10 @@ int cps_objective(cps_handle *h, const void *x, int64_t n, int64_t k, int dtype,
 /* Tuning of the general batched kernel.  Fill with cps_default_batch_options first (1024 threads,
  * split capacity 2^17, final threshold 4096, split fraction 1, 2^12 bins, count first, the
  * sampled bracket, one workgroup per array);
- * 0 fields pick the tuned (or default) value.  With the defaults (or no options) the batch is
- * selected by other kernels, which read every array once, share large arrays among
- * workgroups and leave only the arrays whose sampled interval missed to the general one.
+ * 0 fields pick the tuned (or default) value.  With the defaults (given, kept by the autotuner,
+ * or no options on a handle that was never tuned) the batch is selected by other kernels, which
+ * read every array once, share large arrays among workgroups and leave only the arrays whose
+ * sampled interval missed to the general one.
  * block_threads:   workgroup size, 256, 512 or 1024 (one workgroup runs one array at a time).
  * blocks_per_cu:   resident workgroups per compute unit.
  * split_capacity:  elements of each of a workgroup's two split buffers; a bracket is split

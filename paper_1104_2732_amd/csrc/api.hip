@@ -366,9 +366,25 @@ int check_common(cps_handle *h, const void *x, int64_t n, int64_t k, int dtype) 
 
 // ---- batched selection
 
+// Whether these options of a batched call are the defaults (a copy capacity of more than the default
+// asks for no other method: the default selection needs none).
+bool default_batch(const cps_batch_options &o) {
+  cps_batch_options d;
+  cps_default_batch_options(&d);
+  return (o.block_threads == 0 || o.block_threads == d.block_threads) && o.blocks_per_cu == 0 &&
+         (o.split_capacity == 0 || o.split_capacity == d.split_capacity) &&
+         (o.final_threshold == 0 || o.final_threshold == d.final_threshold) &&
+         (o.maxit == 0 || o.maxit == d.maxit) && o.partition_fraction == d.partition_fraction &&
+         o.hist_bits == d.hist_bits && o.count_first != 0 && o.proposal == 1 &&
+         (o.blocks_per_array == 0 || o.blocks_per_array == 1) &&
+         (o.elements_per_block == 0 || o.elements_per_block == d.elements_per_block) &&
+         (o.team_capacity == 0 || o.team_capacity >= d.team_capacity);
+}
+
 struct BatchResolved {
   cps::CpConfig cfg;
   int grid, block;
+  bool one_read;                // the options in force are the defaults: the default selection
   int64_t cap, ws_stride, gb_off;
   int32_t proposal, team_max;
   int64_t team_chunk, team_cap, team_records;
@@ -383,6 +399,7 @@ int resolve_batched(cps_handle *h, int dtype, int64_t count, const cps_batch_opt
   const int di = dtype == CPS_F32 ? 0 : 1;
   if (opt) o = *opt;
   else if (h->has_tuned[di]) o = h->tuned[di];
+  r.one_read = default_batch(o);
   if (o.block_threads == 0) o.block_threads = 1024;
   if (o.block_threads != 256 && o.block_threads != 512 && o.block_threads != 1024) return CPS_EINVAL;
   if (o.blocks_per_cu < 0 || o.split_capacity < 0 || o.final_threshold < 0 || o.maxit < 0 ||
@@ -436,22 +453,6 @@ int resolve_batched(cps_handle *h, int dtype, int64_t count, const cps_batch_opt
   return CPS_OK;
 }
 
-// Whether the options of a batched call are the defaults (a copy capacity of more than the default
-// asks for no other method: the default selection needs none).
-bool default_batch(const cps_batch_options *o) {
-  if (!o) return true;
-  cps_batch_options d;
-  cps_default_batch_options(&d);
-  return (o->block_threads == 0 || o->block_threads == d.block_threads) && o->blocks_per_cu == 0 &&
-         (o->split_capacity == 0 || o->split_capacity == d.split_capacity) &&
-         (o->final_threshold == 0 || o->final_threshold == d.final_threshold) &&
-         (o->maxit == 0 || o->maxit == d.maxit) && o->partition_fraction == d.partition_fraction &&
-         o->hist_bits == d.hist_bits && o->count_first != 0 && o->proposal == 1 &&
-         (o->blocks_per_array == 0 || o->blocks_per_array == 1) &&
-         (o->elements_per_block == 0 || o->elements_per_block == d.elements_per_block) &&
-         (o->team_capacity == 0 || o->team_capacity >= d.team_capacity);
-}
-
 template <typename T>
 int run_batched(cps_handle *h, const void *const *ptrs, const int64_t *sizes, const int64_t *ks,
                 int64_t count, const cps_batch_options *opt, cps_result *out, double *ksum,
@@ -483,7 +484,7 @@ int run_batched(cps_handle *h, const void *const *ptrs, const int64_t *sizes, co
   a.teams = h->tws;
   a.ksum = ksum;
   a.list = a.list_count = nullptr;
-  if (!default_batch(opt)) {
+  if (!r.one_read) {
     hipError_t e = cps::launch_batched<T>(a, r.grid, r.block, stream);
     return e == hipSuccess ? CPS_OK : hip_fail(e);
   }
