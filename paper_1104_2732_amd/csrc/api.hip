@@ -141,6 +141,7 @@ int ensure_buffer(void *&buf, size_t &have, size_t bytes, hipStream_t stream) {
   size_t want = align_up(bytes + bytes / 8, 1 << 20);
   e = hipMalloc(&buf, want);
   if (e != hipSuccess) {
+    (void)hipGetLastError();  // (not the next launch's)
     g_last_hip = (int)e;
     buf = nullptr;
     return CPS_ENOMEM;
@@ -149,6 +150,19 @@ int ensure_buffer(void *&buf, size_t &have, size_t bytes, hipStream_t stream) {
   if (e != hipSuccess) return hip_fail(e);
   have = want;
   return CPS_OK;
+}
+
+// Whether that would find the memory (a workspace that has another way when it does not stays as
+// it is).
+bool can_grow(size_t have, size_t bytes, hipStream_t stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (bytes <= have) return true;
+  if (stream != nullptr &&
+      (hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone))
+    return false;
+  size_t free_bytes = 0, total = 0;
+  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) return false;
+  return bytes + bytes / 8 <= free_bytes + have;
 }
 
 // The team records of the batched kernel: allocated and zeroed once per handle (every use
@@ -742,18 +756,31 @@ int knn_mean_ex(cps_handle *h, const float *P_dev, const float *f_dev, const flo
     // sampled distances, brackets, counters, ordinate sums, kept distances and ordinates
     std::lock_guard<std::mutex> lk(h->mu);
     cps::KnnFilterBufs w;
-    bool screen;
-    cps::knn_filter_shape(n, dim, nq, k, h->cu_count, &w.nseg, &w.seg, &screen);
-    const size_t off_ab = align_up((size_t)nq * 16384 * sizeof(float), 256);
-    const size_t off_cnt = off_ab + align_up((size_t)nq * 2 * sizeof(float), 256);
-    const size_t off_fs = off_cnt + align_up((size_t)nq * cps::kKnnCntStride * sizeof(uint32_t), 256);
-    const size_t off_ctr = off_fs + align_up((size_t)nq * sizeof(double), 256);
-    const size_t off_k = off_ctr + 256;
-    const size_t off_a = off_k + align_up((size_t)nq * cps::kKnnKeptCap * 2 * sizeof(float), 256);
-    const size_t off_b = off_a + (screen ? align_up((size_t)cps::knn_split_elems(n, dim) * 2, 256) : 0);
-    const size_t off_t = off_b + (screen ? align_up((size_t)nq * 64 * 2, 256) : 0);
-    const size_t bytes = off_t + (screen ? align_up((size_t)nq * sizeof(float), 256) : 0);
-    int rc = ensure_buffer(h->lws, h->lws_bytes, bytes, s);
+    size_t off_ab, off_cnt, off_fs, off_ctr, off_k, off_a, off_b, off_t, bytes;
+    auto layout = [&](bool screen) {
+      cps::knn_filter_shape(n, dim, nq, screen, h->cu_count, &w.nseg, &w.seg);
+      off_ab = align_up((size_t)nq * 16384 * sizeof(float), 256);
+      off_cnt = off_ab + align_up((size_t)nq * 2 * sizeof(float), 256);
+      off_fs = off_cnt + align_up((size_t)nq * cps::kKnnCntStride * sizeof(uint32_t), 256);
+      off_ctr = off_fs + align_up((size_t)nq * sizeof(double), 256);
+      off_k = off_ctr + 256;
+      off_a = off_k + align_up((size_t)nq * cps::kKnnKeptCap * 2 * sizeof(float), 256);
+      off_b = off_a + (screen ? align_up((size_t)cps::knn_split_elems(n, dim) * 2, 256) : 0);
+      off_t = off_b + (screen ? align_up((size_t)nq * 64 * 2, 256) : 0);
+      bytes = off_t + (screen ? align_up((size_t)nq * sizeof(float), 256) : 0);
+    };
+    // The screen's operands grow with n (64 bytes a point in 8 dimensions).  Where they cannot be
+    // had (no memory, or a capture on a handle that has not taken such a call before) the plain
+    // filter serves, whose workspace depends on nq alone.
+    bool screen = cps::knn_use_screen(n, k);
+    layout(screen);
+    int rc = screen && !can_grow(h->lws_bytes, bytes, s) ? CPS_ENOMEM
+                                                        : ensure_buffer(h->lws, h->lws_bytes, bytes, s);
+    if (screen && (rc == CPS_ENOMEM || rc == CPS_ECAPTURE)) {
+      screen = false;
+      layout(false);
+      rc = ensure_buffer(h->lws, h->lws_bytes, bytes, s);
+    }
     if (rc) return rc;
     char *base = (char *)h->lws;
     w.Ds = (float *)base;

@@ -263,8 +263,9 @@ constexpr int64_t kKnnKeptCap = 8128;
 // each other (with 1024 queries' cursors on 32 lines, taking the 460 000 places of 1024
 // queries x 2^20 points, k = 64, added ~107 us to a filter of 268 us)
 constexpr int64_t kKnnCntStride = 32;
-void knn_filter_shape(int64_t n, int32_t dim, int64_t nq, int64_t k, int cu_count, int64_t *nseg,
-                      int64_t *seg, bool *screen);
+bool knn_use_screen(int64_t n, int64_t k);
+void knn_filter_shape(int64_t n, int32_t dim, int64_t nq, bool screen, int cu_count, int64_t *nseg,
+                      int64_t *seg);
 int64_t knn_split_elems(int64_t n, int32_t dim);
 hipError_t launch_knn_filtered(const float *P, const float *f, const float *Q, int64_t n,
                                int32_t dim, int64_t nq, int64_t k, const KnnFilterBufs &w,

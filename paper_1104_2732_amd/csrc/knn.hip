@@ -785,7 +785,7 @@ __global__ __launch_bounds__(kKnnBlock) void knn_select_kernel(
 // filter: 1024 queries x 2^17 points x 8, 3.6 % of the points below the end 216 against 245 us,
 // 4.3 % 271 against 274, 6.6 % 326 against 300; 1024 x 40000 x 5, 4.3 % 147 against 245, 14 %
 // 224 against 268; the line is at the first one's crossing.
-static bool knn_use_screen(int64_t n, int64_t k) {
+bool knn_use_screen(int64_t n, int64_t k) {
   const double S = (double)sample_runs(n) * kPropRun, p = ((double)k - 0.5) / (double)n;
   return p + 4.0 * sqrt(p * (1.0 - p) / S) + 2.0 / S <= kScrPart;
 }
@@ -811,10 +811,9 @@ int64_t knn_split_elems(int64_t n, int32_t dim) {
   return rows * screen_steps(dim) * kScrK;
 }
 
-void knn_filter_shape(int64_t n, int32_t dim, int64_t nq, int64_t k, int cu_count, int64_t *nseg,
-                      int64_t *seg, bool *screen) {
-  *screen = knn_use_screen(n, k);
-  if (*screen) {
+void knn_filter_shape(int64_t n, int32_t dim, int64_t nq, bool screen, int cu_count, int64_t *nseg,
+                      int64_t *seg) {
+  if (screen) {
     // kScrPerCu workgroups per CU over (segments x groups of queries);
     // segments of whole tiles, at most 2^24 points (a pair's place in its 32-bit list word)
     const ScreenShape s = knn_screen_shape(dim, nq);
