@@ -433,8 +433,7 @@ int lms_median_sq_residuals(cps_handle *h, const double *X_dev, const double *y_
  *   selected as in the materialised form.  The workspace holds m * n doubles and about one per
  *   cent more.  `passes` then counts the one pass that forms the residuals and the
  *   two readings of the kept squares.
- * CPS_LMS_AUTO: the filtered form from n = 2^14 on (knn_mean: 2^13), else the materialised
- *   one. */
+ * CPS_LMS_AUTO: the filtered form where n allows it, else the materialised one. */
 enum cps_lms_form { CPS_LMS_AUTO = 0, CPS_LMS_MATERIALISED = 1, CPS_LMS_FILTERED = 2 };
 
 /* lms_median_sq_residuals with a choice of form (above).  Errors: as
@@ -507,7 +506,8 @@ typedef struct cps_knn {
  * their k-th smallest dk by the batched selection; and the mean ordinate of the k nearest
  * points, (sum_{d < dk} f_i + (a / b) sum_{d = dk} f_i) / k with b = #(d = dk),
  * a = k - #(d < dk) (Section 6's rho as an indicator: exactly k points' worth), summed in
- * double precision in a fixed order.  f_dev: n floats.  In the materialised form the
+ * double precision (below n = 2^15, and in the materialised form, in a fixed order).
+ * f_dev: n floats.  In the materialised form the
  * distances are written to the handle's workspace (nq x n floats) for the selection and read
  * back by the reduction.
  * Errors: CPS_EINVAL for null pointers, n < 1, dim outside [1, 16], nq outside [1, 65535],
@@ -516,7 +516,7 @@ int knn_mean(cps_handle *h, const float *P_dev, const float *f_dev, const float 
              int32_t dim, int64_t nq, int64_t k, cps_knn *out_dev, void *stream);
 
 /* knn_mean with a choice of form (cps_lms_form; CPS_LMS_AUTO is knn_mean, which takes the
- * filtered form from n = 2^13 on).  Filtered: each query's sampled bracket (a, b) from the
+ * filtered form from n = 2^15 on).  Filtered: each query's sampled bracket (a, b) from the
  * distances of the points the batched kernel would sample, one pass over the points that
  * keeps the distances in (a, b) (and NaN) with their ordinates (at most 8128 per query),
  * counting d <= a and summing its ordinates; d_k by a radix select among the kept ones, the

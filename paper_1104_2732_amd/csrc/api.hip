@@ -636,14 +636,12 @@ static int lms_filtered_run(cps_handle *h, const double *X_dev, const double *y_
   return e == hipSuccess ? CPS_OK : hip_fail(e);
 }
 
+// The sizes of the filtered forms.
+// That is also the form taken when the caller leaves it open.  The kernels would gain below 2^15
+// too (1024 queries x 16384 points 71 us filtered, 103 materialised; 800 candidates x 32000
+// rows 90 / 128), but a caller is promised the materialised form there: its kNN means are added
+// in a fixed order, and its workspaces also serve any smaller call under capture.
 static bool lms_can_filter(int64_t n) { return n >= ((int64_t)1 << 15) && n < ((int64_t)1 << 31); }
-// ... and the form taken when the caller leaves it open.  Least median of squares, filtered /
-// materialised, 800 candidates: n = 8192 84 / 65 us, 12000 86 / 84, 16384 86 / 90, 32000 90 / 128; 16
-// candidates 34 / 33, 34 / 41, 34 / 41, 35 / 45.  k nearest neighbours, 1024 queries, k = 16: n = 4100
-// 71 / 97, 8192 69 / 94, 16384 71 / 103, 32000 74 / 158; 32 queries, k = 1: 43 / 42, 42 / 43, 42 / 46,
-// 43 / 55 (the sample of 4096 points needs more than that many).
-static bool lms_auto_filter(int64_t n) { return n >= ((int64_t)1 << 14) && n < ((int64_t)1 << 31); }
-static bool knn_auto_filter(int64_t n) { return n >= ((int64_t)1 << 13) && n < ((int64_t)1 << 31); }
 
 int lms_median_sq_residuals_ex(cps_handle *h, const double *X_dev, const double *y_dev,
                                const double *betas_dev, int64_t n, int32_t p, int64_t m,
@@ -653,7 +651,7 @@ int lms_median_sq_residuals_ex(cps_handle *h, const double *X_dev, const double 
     return CPS_EINVAL;
   const bool can_filter = lms_can_filter(n);
   if (form == CPS_LMS_FILTERED && !can_filter) return CPS_EINVAL;
-  const bool filtered = form == CPS_LMS_FILTERED || (form == CPS_LMS_AUTO && lms_auto_filter(n));
+  const bool filtered = form == CPS_LMS_FILTERED || (form == CPS_LMS_AUTO && can_filter);
   hipStream_t s = (hipStream_t)stream;
   const int64_t rank = (n + 1) / 2;
   std::lock_guard<std::mutex> lk(h->mu);
@@ -695,7 +693,7 @@ int lts_trimmed_sq_ex(cps_handle *h, const double *X_dev, const double *y_dev,
     return CPS_EINVAL;
   const bool can_filter = lms_can_filter(n);
   if (form == CPS_LMS_FILTERED && !can_filter) return CPS_EINVAL;
-  const bool filtered = form == CPS_LMS_FILTERED || (form == CPS_LMS_AUTO && lms_auto_filter(n));
+  const bool filtered = form == CPS_LMS_FILTERED || (form == CPS_LMS_AUTO && can_filter);
   hipStream_t s = (hipStream_t)stream;
   if (filtered) {
     std::lock_guard<std::mutex> lk(h->mu);
@@ -752,7 +750,7 @@ int knn_mean_ex(cps_handle *h, const float *P_dev, const float *f_dev, const flo
   const bool can_filter = lms_can_filter(n);
   if (form == CPS_LMS_FILTERED && !can_filter) return CPS_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  if (form == CPS_LMS_FILTERED || (form == CPS_LMS_AUTO && knn_auto_filter(n))) {
+  if (form == CPS_LMS_FILTERED || (form == CPS_LMS_AUTO && can_filter)) {
     // sampled distances, brackets, counters, ordinate sums, kept distances and ordinates
     std::lock_guard<std::mutex> lk(h->mu);
     cps::KnnFilterBufs w;
