@@ -603,7 +603,8 @@ int cps_mlp_forward(cps_handle *h, const float *params_dev, const float *feat_de
 /* Mean training loss (loss_dev: one float, may be NULL) and its gradient (grad_dev:
  * CPS_MLP_PARAMS floats) over `count` examples (feature rows and labels ustar_dev),
  * by back-propagation in float with a fixed summation order (deterministic).  Uses the
- * handle's workspace (about count / 32 x 35 KB). */
+ * handle's workspace (about min(count, 4096) / 4 x 35 KB, or count / 32 x 35 KB where that is
+ * more). */
 int cps_mlp_loss_grad(cps_handle *h, const float *params_dev, const float *feat_dev,
                       const float *ustar_dev, int64_t count, float *grad_dev, float *loss_dev,
                       void *stream);

@@ -717,9 +717,11 @@ hipError_t launch_mlp_forward(const float *P, const float *feat, int64_t count, 
 }
 
 size_t mlp_grad_workspace(int64_t count) {
-  const int64_t per = count <= kMlpFew ? kFewEx : kEPW;
-  const int64_t nwg = (count + per - 1) / per;
-  return (size_t)nwg * (kParams + 1) * sizeof(float) + 256;
+  // (what serves a minibatch serves every smaller one: a call that was captured after a larger one
+  // must not have to allocate)
+  const int64_t few = ((count < kMlpFew ? count : kMlpFew) + kFewEx - 1) / kFewEx;
+  const int64_t all = (count + kEPW - 1) / kEPW;
+  return (size_t)(all > few ? all : few) * (kParams + 1) * sizeof(float) + 256;
 }
 
 hipError_t launch_mlp_loss_grad(const float *P, const float *feat, const float *ustar,
