@@ -56,10 +56,11 @@ struct SelectLayout {
   int64_t slot_stride, seg_R, zcap, smp_n;
 };
 
-// quick: with the one-read selection's parts (its counters and bins, which every call leaves
-// zero, before anything that moves with the size: inside the cleared first part).
+// slots: the one-read selection's gather slots (one per workgroup), with its counters and bins
+// (which every call leaves zero, before anything that moves with the size: inside the cleared
+// first part); -1: neither.
 SelectLayout select_layout(int64_t seg_R, int grid, int64_t zcap, int gmax, size_t esize,
-                           int64_t smp_n = 0, bool quick = false) {
+                           int64_t smp_n = 0, int64_t slots = -1) {
   SelectLayout L;
   size_t off = 0;
   L.st = off;
@@ -70,7 +71,7 @@ SelectLayout select_layout(int64_t seg_R, int grid, int64_t zcap, int gmax, size
   off = align_up(off + cps::kHistWords * sizeof(uint64_t), 256);
   L.slot_stride = gmax;
   L.qsync = L.qhist = L.qrec = L.qslot = L.qkept = L.qcnt = off;
-  if (quick) {
+  if (slots >= 0) {
     off = align_up(off + sizeof(cps::SyncCtl), 256);
     L.qhist = off;
     off = align_up(off + (size_t)cps::kQuickCopies * cps::kHistMaxBins * sizeof(uint32_t), 256);
@@ -100,7 +101,7 @@ SelectLayout select_layout(int64_t seg_R, int grid, int64_t zcap, int gmax, size
   L.sm = off;
   off = align_up(off + (size_t)smp_n * esize, 256);
   L.zq = off;
-  if (quick) off = align_up(off + (size_t)gmax * cps::kQuickGather * esize, 256);
+  if (slots > 0) off = align_up(off + (size_t)slots * cps::kQuickGather * esize, 256);
   L.total = off;
   return L;
 }
@@ -291,6 +292,16 @@ bool default_method(const cps_options *opt) {
 // 81, 1 GiB 231 / 392, 2 GiB float64 413 / 725.
 constexpr size_t kQuickCopyBytes = (size_t)1 << 26;
 
+// The one-read selection's workgroups for n elements (none: one workgroup's registers hold them, or
+// its 32-bit counts do not).  Every layout for n has their slots, whatever the call's options, so
+// that what one call of n leaves serves any other.
+template <typename T> int64_t quick_slots(int64_t n, int gmax) {
+  if (n <= cps::quick_small_max<T>() || n > cps::kQuickMaxN) return 0;
+  const int64_t tile = (int64_t)cps::kSelectBlock * cps::kSelectUnroll * (16 / (int64_t)sizeof(T));
+  const int64_t tiles = (n + tile - 1) / tile;
+  return tiles < gmax ? tiles : gmax;
+}
+
 // bracket_dev: a device-side proposal (a, b, use) read by pass 0, or null.
 template <typename T>
 int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_options *opt,
@@ -310,9 +321,11 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
     return e == hipSuccess ? CPS_OK : hip_fail(e);
   }
   const int per_cu = sizeof(T) == 4 ? h->max_blocks_f32 : h->max_blocks_f64;
-  const bool quick = plain && k > 1 && k < n && n <= cps::kQuickMaxN && r.grid <= 1024;
-  const SelectLayout L = select_layout(r.seg_R, r.grid, r.cfg.zcap, h->cu_count * per_cu, sizeof(T),
-                                       spec_sample_elems(n, sizeof(T), r.cfg.spec_min_n), true);
+  const int gmax = h->cu_count * per_cu;
+  const int64_t slots = quick_slots<T>(n, gmax);
+  const bool quick = plain && k > 1 && k < n && r.grid <= slots && r.grid <= 1024;
+  const SelectLayout L = select_layout(r.seg_R, r.grid, r.cfg.zcap, gmax, sizeof(T),
+                                       spec_sample_elems(n, sizeof(T), r.cfg.spec_min_n), slots);
   rc = ensure_workspace(h, L.total, stream);
   if (rc) return rc;
   char *base = (char *)h->ws;
@@ -1015,9 +1028,11 @@ int cps_reserve(cps_handle *h, int64_t n, int dtype) {
   int rc = resolve(h, n, dtype, nullptr, r);
   if (rc) return rc;
   const int per_cu = dtype == CPS_F32 ? h->max_blocks_f32 : h->max_blocks_f64;
+  const int gmax = h->cu_count * per_cu;
   const SelectLayout L =
-      select_layout(r.seg_R, r.grid, r.cfg.zcap, h->cu_count * per_cu, dtype_size(dtype),
-                    spec_sample_elems(n, dtype_size(dtype), r.cfg.spec_min_n), true);
+      select_layout(r.seg_R, r.grid, r.cfg.zcap, gmax, dtype_size(dtype),
+                    spec_sample_elems(n, dtype_size(dtype), r.cfg.spec_min_n),
+                    dtype == CPS_F32 ? quick_slots<float>(n, gmax) : quick_slots<double>(n, gmax));
   return ensure_workspace(h, L.total, nullptr);
 }
 
