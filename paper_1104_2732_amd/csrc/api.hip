@@ -316,10 +316,6 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
   // Median of normal data, this way / the general kernel: float32 2^8 7 / 22 us, 2^14 7 / 55, 2^16
   // 22 / 59, 2^20 28 / 66, 2^24 43 / 122, 2^28 228 / 454; float64 2^15 18 / 97, 2^28 413 / 808.
   const bool plain = stats == nullptr && bracket_dev == nullptr && default_method(opt);
-  if (plain && n <= cps::quick_small_max<T>()) {
-    const hipError_t e = cps::launch_quick_small<T>(x, n, k, out, stream);
-    return e == hipSuccess ? CPS_OK : hip_fail(e);
-  }
   const int per_cu = sizeof(T) == 4 ? h->max_blocks_f32 : h->max_blocks_f64;
   const int gmax = h->cu_count * per_cu;
   const int64_t slots = quick_slots<T>(n, gmax);
@@ -327,6 +323,12 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
   const SelectLayout L = select_layout(r.seg_R, r.grid, r.cfg.zcap, gmax, sizeof(T),
                                        spec_sample_elems(n, sizeof(T), r.cfg.spec_min_n), slots);
   rc = ensure_workspace(h, L.total, stream);
+  if (plain && n <= cps::quick_small_max<T>() && rc != CPS_EHIP) {
+    // (it needs no workspace; what it leaves serves a later call of n with options or a trace,
+    // which may be under capture)
+    const hipError_t e = cps::launch_quick_small<T>(x, n, k, out, stream);
+    return e == hipSuccess ? CPS_OK : hip_fail(e);
+  }
   if (rc) return rc;
   char *base = (char *)h->ws;
   cps::SelectArgs<T> a;
