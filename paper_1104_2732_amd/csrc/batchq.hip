@@ -36,35 +36,15 @@ constexpr int kBqBlock = 512;
 constexpr int kBqWaves = kBqBlock / kWave;
 template <typename T> constexpr int kBqPer = sizeof(T) == 4 ? 32 : 16;  // keys per lane, small arrays
 template <typename T> constexpr int kBqSmall = kBqBlock * kBqPer<T>;
+static_assert(kBqSmall<float> == bq_small_max(4) && kBqSmall<double> == bq_small_max(8), "the route's line");
 constexpr int kBqSmpA = 8;                       // samples per lane: 4096 in all, or
 template <typename T> constexpr int kBqSmpB = sizeof(T) == 4 ? 32 : 24;  // 16384 (12288)
 constexpr int kBqU = 4;                          // vectors per lane and tile
 constexpr size_t kBqListBytes = 49152;           // LDS for the inside elements
-constexpr int64_t kBqMaxN = (int64_t)1 << 31;    // larger arrays go to the general kernel
 constexpr double kBqDev = 4.5;  // deviations of the interval's ends: a miss in 10^5 arrays
-// Arrays from this many elements on are shared by workgroups: smaller ones keep their inside
-// elements in LDS.  The interval holds 3.6 % of the elements at most with float32's large sample
-// (4.1 % with float64's), 7.1 % with the small one: 9300 of 12288 places (2700 of 6144).
-template <typename T> constexpr int64_t kBqShare = (int64_t)1 << (sizeof(T) == 4 ? 18 : 16);
-
-template <typename T> CPS_HD inline bool bq_big_sample(int64_t n) { return n >= kBqShare<T> / 2; }
-template <typename T> CPS_HD inline bool bq_shared(int64_t n) { return n >= kBqShare<T> && n <= kBqMaxN; }
-// A shared array's region of the pool: room for a sixteenth of its elements (the interval holds
-// 3.6 % of them, of float64 4.1 %, give or take 5 % of that), then the key bins of each part.
-// Arrays that find no region are left to the general kernel unread.
-CPS_HD inline int64_t bq_room(int64_t n) { return (n / 16 + 63) / 64 * 64; }
-constexpr int kBqBins = 4 * kBqBlock, kBqBinsLog2 = quick_bins_log2(kBqBlock);
-template <typename T> CPS_HD inline int64_t bq_region(int64_t n, uint32_t parts) {
-  return bq_room(n) + (int64_t)parts * (int64_t)(kBqBins * sizeof(uint32_t) / sizeof(T));
-}
-
-// Eight size classes per power of two; the limit of sharing is a class limit, so the shared
-// arrays come before all others (what is left to the general kernel comes last).
-CPS_HD inline int bq_class(int64_t n) {
-  if (n < 8 || n > kBqMaxN) return n < 0 || n > kBqMaxN ? 0 : (int)n;
-  const int e = 63 - __builtin_clzll((unsigned long long)n);
-  return (e - 2) * 8 + (int)((n >> (e - 3)) & 7);  // (at most 239)
-}
+template <typename T> CPS_HD inline bool bq_big_sample(int64_t n) { return n >= bq_share(sizeof(T)) / 2; }
+constexpr int kBqBinsLog2 = quick_bins_log2(kBqBlock);
+static_assert(kBqBins == 4 * kBqBlock, "four bins per thread");
 
 // ------------------------------------------------------------------ the order of the arrays
 
@@ -97,15 +77,14 @@ __global__ __launch_bounds__(1024) void batchq_order_kernel(BatchqArgs<T> a, int
     if (tid + p * BLOCK < count) {
       size[tid + p * BLOCK] = n[p];
       atomicAdd(&cls[255 - bq_class(n[p])], 1u);
-      all += n[p] > 0 && n[p] <= kBqMaxN ? (double)n[p] : 0.0;
+      all += bq_weight(n[p]);
     }
   all = wave_sum(all);
   if (tid % kWave == 0) wtot[tid / kWave] = all;
   __syncthreads();
   all = 0.0;
   for (int w = 0; w < BLOCK / kWave; ++w) all += wtot[w];
-  const int64_t half = (int64_t)(all / (2.0 * grid));
-  const int64_t part = half > kBqShare<T> ? half : kBqShare<T>;
+  const int64_t part = bq_part(all, grid, sizeof(T));
   const uint32_t c = tid < 256 ? cls[tid] : 0u;
   const uint32_t at = block_scan_u32<BLOCK>(c, wsum);
   if (tid < 256) cls[tid] = at;
@@ -119,18 +98,16 @@ __global__ __launch_bounds__(1024) void batchq_order_kernel(BatchqArgs<T> a, int
   // slots tid * PER ..: first items and regions (in units of 64 elements; what passes the pool's
   // end gets none; 4096 slots of at most 2^20 - 1 units stay below 2^32)
   uint32_t parts[PER], units[PER], sp = 0, su = 0, st = 0, sti = 0;
-  const uint64_t pool_units = (uint64_t)a.pool_elems / 64;
-  const uint32_t most = (uint32_t)(pool_units < (1u << 20) - 2 ? pool_units : (1u << 20) - 2) + 1;
+  const uint32_t most = bq_most_units(a.pool_elems);
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
     const int i = tid * PER + p;
     const int64_t m = i < count ? size[order[i]] : 0;
     parts[p] = i < count ? 1u : 0u;
     units[p] = 0;
-    if (i < count && bq_shared<T>(m)) {
-      parts[p] = (uint32_t)((m + part - 1) / part);
-      const int64_t u = bq_region<T>(m, parts[p]) / 64;
-      units[p] = u < (int64_t)most ? (uint32_t)u : most;
+    if (i < count && bq_shared(m, sizeof(T))) {
+      parts[p] = bq_parts(m, part);
+      units[p] = bq_units(m, parts[p], most, sizeof(T));
       st += 1;
       sti += parts[p];
     }
@@ -146,7 +123,7 @@ __global__ __launch_bounds__(1024) void batchq_order_kernel(BatchqArgs<T> a, int
   if (tid == BLOCK - 1) total[0] = f + sp;
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const bool fits = ((int64_t)u + units[p]) * 64 <= a.pool_elems && units[p] < most;
+    const bool fits = bq_fits(u, units[p], most, a.pool_elems);
     first[tid * PER + p] = f;
     unit[tid * PER + p] = fits ? u : ~0u;
     npart[tid * PER + p] = parts[p];
@@ -168,7 +145,7 @@ __global__ __launch_bounds__(1024) void batchq_order_kernel(BatchqArgs<T> a, int
       s.parts = npart[i];
       s.pad = 0u;
       a.slot[i] = s;
-      if (bq_shared<T>(s.n)) {
+      if (bq_shared(s.n, sizeof(T))) {
         BatchqRec r = {};
         r.region = unit[i] != ~0u ? (int64_t)unit[i] * 64 : -1;
         a.rec[i] = r;
@@ -558,17 +535,10 @@ __global__ __launch_bounds__(kBqBlock, 4) void batchq_kernel(BatchqArgs<T> a) {
   for (;;) {
     if (tid < kWave) {
       const uint32_t q = (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
-      uint32_t slot = q - team_items + teams;
-      if (q < team_items) {  // the last shared array whose first item is not after q
-        uint32_t s = 0;
-#pragma unroll
-        for (uint32_t w = kWave; w > 0; w /= kWave) {
-          const uint32_t t = s + lane * w;
-          const uint64_t m = ballot(t < teams && a.slot[t < teams ? t : 0].first <= q);
-          s += (popc(m) - 1) * w;
-        }
-        slot = s;
-      }
+      const uint32_t slot = bq_slot(q, teams, team_items, [&](uint32_t s, uint32_t w) {
+        const uint32_t t = s + lane * w;
+        return popc(ballot(t < teams && a.slot[t < teams ? t : 0].first <= q));
+      });
       if (lane == 0) {
         sh.item = q;
         if (q < items) {
@@ -597,7 +567,7 @@ __global__ __launch_bounds__(kBqBlock, 4) void batchq_kernel(BatchqArgs<T> a) {
     } else if (n <= kBqSmall<T>) {
       bq_small<T, kBqPer<T>, SUM>(a, j, x, (int)n, k, sh);
     } else {
-      bq_large<T, SUM>(a, j, x, n, k, part, parts, bq_shared<T>(n) ? a.rec + sh.slot.pad : nullptr, sh);
+      bq_large<T, SUM>(a, j, x, n, k, part, parts, bq_shared(n, sizeof(T)) ? a.rec + sh.slot.pad : nullptr, sh);
     }
     __syncthreads();
   }
