@@ -448,13 +448,17 @@ __device__ inline SampleEnds<typename Traits<T>::Key> sample_ends(
   if (e.kb == hole) --e.kb;
   e.ia = e.ka;
   e.ib = e.kb;
-  if (!open0 && sh0 == 0) {
-    ++e.ia;
-    if (e.ia == hole) ++e.ia;
-  }
-  if (!open1 && sh1 == 0 && e.kb != e.ka) {
-    --e.ib;
-    if (e.ib == hole) --e.ib;
+  if (e.ka == kpos) {
+    --e.ib;  // (nothing lies above +inf: repeated, it is the upper end)
+  } else {
+    if (!open0 && sh0 == 0) {
+      ++e.ia;
+      if (e.ia == hole) ++e.ia;
+    }
+    if (!open1 && sh1 == 0 && e.kb != e.ka) {
+      --e.ib;
+      if (e.ib == hole) --e.ib;
+    }
   }
   __syncthreads();
   return e;
