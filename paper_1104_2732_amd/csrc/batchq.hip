@@ -512,6 +512,9 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
       bq_write<T>(a, jj, 0, 0, 0, 0.0, n, k, true);
     } else if (ri < 1) {
       bq_write<T>(a, jj, e.ka, lt, ca, blw, n, k, false);
+    } else if (ri <= inner && equal == 0) {
+      write_selection(a.out + jj, 0, __builtin_nan(""), 0, 0, n, 1, ST_INTERNAL);
+      if (a.ksum) a.ksum[jj] = __builtin_nan("");
     } else if (ri <= inner) {
       const double s = blw + (ca ? (double)ca * (double)f.va : 0.0) + lsum;
       bq_write<T>(a, jj, key, lt + ca + less, equal, s, n, k, false);

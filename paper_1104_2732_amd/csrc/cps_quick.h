@@ -204,7 +204,9 @@ __device__ inline void write_key(cps_result *out, typename Traits<T>::Key key, i
 // The element of rank r (1-based) among the elements that `walk` visits, all with keys in [klo,
 // khi], from their counts in this thread's four key bins (range_shift of the range): the rank's
 // bin, split again while it holds many elements, then ranked by comparing each with all.
-// `hist` is 4 BLOCK words of LDS, `fin` kWalkFinal keys.
+// `hist` is 4 BLOCK words of LDS, `fin` kWalkFinal keys.  `equal` is 0 where the counts and the
+// elements disagree, as when the input changes during the call (no bin holds the rank, or not as
+// many elements as its bin counted).
 constexpr uint32_t kWalkFinal = 256;
 CPS_HD constexpr int quick_bins_log2(int block) { return block == 1024 ? 12 : (block == 512 ? 11 : 10); }
 template <typename T, int BLOCK, typename Walk>
@@ -220,6 +222,7 @@ __device__ inline void walk_select(Walk &&walk, uint32_t (&h)[4], int64_t r,
   // (each round narrows the range by the bins' bits: seven at most)
   for (int round = 0; round < 8; ++round) {
     const int shift = range_shift((uint64_t)(khi - klo), quick_bins_log2(BLOCK));
+    if (tid == 0) sh.inb[0] = 0u;
     const uint32_t cum = block_scan_u32<BLOCK>(h[0] + h[1] + h[2] + h[3], sh.wsum);
     pick4<BLOCK>(h, cum, (uint32_t)r, 0, sh);
     __syncthreads();
@@ -252,7 +255,7 @@ __device__ inline void walk_select(Walk &&walk, uint32_t (&h)[4], int64_t r,
     h[3] = q.w;
   }
   if (cnt > (int64_t)kWalkFinal) cnt = kWalkFinal;
-  if (tid == 0) sh.cursor = 0u;
+  if (tid == 0) sh.cursor = sh.equal = 0u;
   __syncthreads();
   walk([&](T v, bool ok) {
     const Key q = Traits<T>::key(v), d = q - klo;
@@ -279,7 +282,7 @@ __device__ inline void walk_select(Walk &&walk, uint32_t (&h)[4], int64_t r,
   __syncthreads();
   key = (Key)sh.key;
   less += sh.less;
-  equal = sh.equal;
+  equal = sh.cursor == (uint32_t)cnt ? sh.equal : 0u;
 }
 
 // A value every lane of the wavefront holds, moved to scalar registers.

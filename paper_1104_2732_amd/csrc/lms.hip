@@ -525,6 +525,13 @@ __global__ __launch_bounds__(kLmsSelBlock, 8) void lms_select_kernel(
   uint64_t key;
   int64_t less, equal;
   walk_select<double, BLOCK>(walk, h, k - below, ka, kb, hist, fin, sh, key, less, equal);
+  if (equal == 0) {  // (uniform)
+    if (tid == 0) {
+      write_selection(out + c, 0, __builtin_nan(""), 0, 0, n, 3, CPS_STATUS_INTERNAL);
+      if (ksum) ksum[c] = __builtin_nan("");
+    }
+    return;
+  }
   if (tid == 0) lms_write_result(out + c, key, below + less, equal, n, 3);
   if (ksum) {  // (uniform)
     const double v = Traits<double>::unkey(key);
