@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcpselect.so")
-SOURCES = ["select.hip", "quick.hip", "batched.hip", "batchq.hip", "lms.hip", "knn.hip", "learned.hip", "noalloc.hip", "api.hip"]
+SOURCES = ["select.hip", "select_quick.hip", "quick.hip", "batched.hip", "batched_list.hip", "batchq.hip", "lms.hip", "knn.hip", "learned.hip", "noalloc.hip", "api.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

@@ -332,7 +332,6 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
   if (rc) return rc;
   char *base = (char *)h->ws;
   cps::SelectArgs<T> a;
-  a.quick = cps::QuickArgs<T>{};
   a.x = x;
   a.n = n;
   a.k = k;
@@ -363,7 +362,7 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
   a.smp_n = L.smp_n;
   hipError_t e;
   if (quick) {
-    cps::QuickArgs<T> &q = a.quick;
+    cps::QuickArgs<T> q;
     q.x = x;
     q.n = n;
     q.k = k;
@@ -379,8 +378,10 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
     q.sync = (cps::SyncCtl *)(base + L.qsync);
     e = cps::launch_quick_filter<T>(q, (size_t)n * sizeof(T) >= kQuickCopyBytes, r.grid, stream);
     if (e != hipSuccess) return hip_fail(e);
+    e = cps::launch_select_quick<T>(a, q, r.grid, stream);
+  } else {
+    e = cps::launch_select<T>(a, r.grid, r.cooperative, stream);
   }
-  e = cps::launch_select<T>(a, r.grid, r.cooperative, stream);
   if (e != hipSuccess) return hip_fail(e);
   return CPS_OK;
 }
@@ -542,7 +543,7 @@ int run_batched(cps_handle *h, const void *const *ptrs, const int64_t *sizes, co
     q.ksum = a.ksum = ksum ? ksum + at : nullptr;
     q.count = a.count = m;
     hipError_t e = cps::launch_batchq<T>(q, h->cu_count * per_cu, stream);
-    if (e == hipSuccess) e = cps::launch_batched<T>(a, r.grid, r.block, stream);
+    if (e == hipSuccess) e = cps::launch_batched_list<T>(a, r.grid, stream);
     if (e != hipSuccess) return hip_fail(e);
   }
   return CPS_OK;

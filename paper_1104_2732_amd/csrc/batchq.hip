@@ -1,6 +1,6 @@
 // The default batched selection: every array is read once.
 //
-// The general batched kernel (batched.hip) gives an array to one workgroup, whose chain of sample,
+// The general batched kernel (batched_kernel.h) gives an array to one workgroup, whose chain of sample,
 // pass 0, histogram passes, gather and radix select costs ~40 us however small the array is, and
 // whose LDS leaves one workgroup per CU, so nothing hides it.  Here:
 //
@@ -8,25 +8,30 @@
 //   selected there;
 // * a larger one is read once against a likely interval of its rank (sample quantiles, as the
 //   single-array filter, quick.hip): elements below are counted, those inside (8 % at most) kept
-//   in LDS, and when the counts prove the interval the select runs among them, in registers;
-// * an array of more than 1 MiB is cut into parts of at most that, taken by any workgroups.  All
+//   in LDS, and when the counts prove the interval the select runs among them;
+// * an array of 2^18 float32 (2^16 float64) elements or more is cut into parts of at least that
+//   many (half a workgroup's share of the batch where that is more), taken by any workgroups.  All
 //   parts take the same sample and so the same interval; each adds its counts to the array's
 //   record and its inside elements to the array's region of a pool, and the last to arrive
 //   selects among them.  Few large arrays then fill the chip like many small ones.
 //
-// An array whose counts do not prove the interval, or whose inside elements found no room, goes on a list
-// that the general kernel works through afterwards, so no result depends on a sample.
+// An array whose counts do not prove the interval, or whose inside elements found no room (or whose
+// region found none in the pool), goes on a list that the general kernel works through afterwards,
+// so no result depends on a sample.
 //
 // Two workgroups of 512 threads per CU: one's latencies (sample 9 us, ends 4, select 6 to 12, next
-// item 3) hide behind the other's streaming.  Three smaller ones (half the tile, spills) were slower:
-// 690 us against 576 for 4096 float32 arrays of 10^3 to 10^6 elements (2.37 GB; the general
-// kernel 1150); 64 arrays of 2^22 elements 314 us (general 1590).  Of the 576 us, a workgroup spends
-// 416 streaming, at the rate that reads mixed with the shared arrays' copies reach (60 us of it
-// is the copies), 70 on samples and their ends, 42 on selects, 19 between items.  Comparing and
-// appending element by element instead of by vectors (RowFilter): 690 us.  With the key bins
-// counted by a walk over the kept elements instead of on the way: 580 and 355 us (the last
-// array's select alone 100 us).  Many large float64 arrays gain least, as their copies are the
-// widest writes: 512 of 2^20 elements 952 us (general 958; with a sample of 8192 for 12288, 970).
+// item 3) hide behind the other's streaming.  Calls: 4096 float32 arrays of 10^3 to 10^6 elements
+// (2.37 GB) 597 us, the general kernel 1156; 64 arrays of 2^22 elements 333 us, the general kernel
+// 1592; of these the order kernel is 22 and 6, the general kernel's empty launch 4.  The
+// comparisons that follow are of the selection's kernel alone, 576 and 314 us when they were made.
+// Three smaller workgroups (half the tile, spills): 690 us for the 4096 arrays.  Of the 576, a
+// workgroup spends 416 streaming, at the rate that reads mixed with the shared arrays' copies
+// reach (60 us of it is the copies), 70 on samples and their ends, 42 on selects, 19 between
+// items.  Comparing and appending element by element instead of by vectors (RowFilter): 690 us.
+// With the key bins counted by a walk over the kept elements instead of on the way: 580 and 355
+// us (the last array's select alone 100 us).  Many large float64 arrays gain least, as their
+// copies are the widest writes: calls of 512 arrays of 2^20 elements 952 us (general 958; with a
+// sample of 8192 for 12288, 970).
 #include "batch_queue.h"
 #include "cps_quick.h"
 

@@ -73,7 +73,7 @@ struct QuickRec {
 template <typename T> struct QuickArgs {
   const T *x;
   int64_t n, k;
-  QuickRec *rec;         // null: no filter ran
+  QuickRec *rec;
   int64_t *slot;         // per workgroup, slot_stride apart: #(x < interval), the two ends'
   int64_t slot_stride;   // repeated values, NaN
   uint32_t *hist;        // kQuickCopies sets of the interval's bins (zero between calls)
@@ -114,7 +114,6 @@ template <typename T> struct SelectArgs {
   T *smp;              // pass 0's sample for the likely interval: the first vector of every
                        // tile of x (smp_n elements), or null
   int64_t smp_n;
-  QuickArgs<T> quick;  // the filter that ran before this kernel (rec null: none)
 };
 
 // ---- batched selection
@@ -168,7 +167,7 @@ template <typename T> struct BatchArgs {
   TeamCtl *teams;        // team_records records
   T *tbuf;               // team_records buffers of team_cap elements
   double *ksum;          // per array: the sum of its k smallest elements (or null)
-  const uint32_t *list;  // only these arrays (indices), *list_count of them; or null: all
+  const uint32_t *list;  // launch_batched_list: only these arrays (indices), *list_count of them
   const uint32_t *list_count;
 };
 
@@ -213,6 +212,8 @@ template <typename T> int batchq_max_blocks_per_cu();
 
 template <typename T>
 hipError_t launch_batched(const BatchArgs<T> &a, int grid, int block, hipStream_t stream);
+// ... over a list of the arrays, 1024 threads per workgroup.
+template <typename T> hipError_t launch_batched_list(const BatchArgs<T> &a, int grid, hipStream_t stream);
 template <typename T> int batched_max_blocks_per_cu(int block);
 
 hipError_t launch_lms_residuals(const double *X, const double *y, const double *betas, int64_t n,
@@ -279,6 +280,11 @@ hipError_t launch_knn_reduce(const float *P, const float *f, const float *Q, con
 
 template <typename T>
 hipError_t launch_select(const SelectArgs<T> &a, int grid, bool cooperative, hipStream_t stream);
+// After the filter.
+template <typename T>
+hipError_t launch_select_quick(const SelectArgs<T> &a, const QuickArgs<T> &quick, int grid,
+                               hipStream_t stream);
+template <typename T> int select_quick_max_blocks_per_cu();
 template <typename T> int select_max_blocks_per_cu();
 template <typename T>
 hipError_t launch_objective(const T *x, int64_t n, int64_t k, const double *ys, int64_t ny,

@@ -1,8 +1,9 @@
 // The sampled bracket: a likely interval for the k-th smallest of n values, from S of them.
 //
-// Used by the batched kernel (its arrays' pass 0 classifies against it) and by the least-
-// median-of-squares filter (which keeps only the residuals inside it).  The counts taken
-// over the whole array decide whether the bracket holds, so no result depends on it.
+// Used by the general batched kernel (its arrays' pass 0 classifies against it); the filtered
+// forms of least median of squares, least trimmed squares and k nearest neighbours sample the
+// same places and take their ends from registers (sample_ends).  The counts taken over the whole
+// array decide whether the bracket holds, so no result depends on it.
 #pragma once
 
 #include "cps_device.h"
@@ -19,7 +20,7 @@ constexpr int64_t kBatchPropMin = (int64_t)1 << 15;
 
 template <typename T> __device__ constexpr int32_t c_dtype() { return sizeof(T) == 4 ? 0 : 1; }
 
-// Sample size for n values (n >= kBatchPropMin), and the distance between the starts of
+// Sample size for n values (n >= kBatchPropMin, which the filtered forms' sizes are too), and the distance between the starts of
 // consecutive runs of kPropRun sampled neighbours: the runs lie inside the n values and do
 // not overlap.
 __device__ __forceinline__ int sample_size(int64_t n) {

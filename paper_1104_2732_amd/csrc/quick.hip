@@ -1,7 +1,7 @@
 // The default selection's own kernels: arrays that one workgroup holds in registers, and the
 // filter that reads a larger array once.
 //
-// Larger arrays.  The general kernel (select.hip) reads x two or three times and its small
+// Larger arrays.  The general kernel (select_kernel.h) reads x two or three times and its small
 // passes cost 10-15 us each, most of it waiting for the grid.  Here one kernel reads x once
 // against a likely interval of the k-th smallest (sample quantiles, so the paper's
 // count-and-compact needs no iterations first): it counts the elements below the interval,
