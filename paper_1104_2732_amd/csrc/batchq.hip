@@ -176,7 +176,7 @@ template <typename T> struct BqShared {
   uint32_t hist[kBqBins];
   typename Traits<T>::Key fin[kWalkFinal];
   uint64_t count[3];  // below, the ends' repeated values
-  double wsum[kBqWaves];
+  Sum2 sums[kBqWaves];
   uint32_t held[kBqWaves], over, item, last;
   BatchqSlot slot;
 };
@@ -193,25 +193,15 @@ __device__ inline void bq_redo(const BatchqArgs<T> &a, uint32_t j) {
   a.redo[at] = j;
 }
 
-// Sum of `v` over the workgroup, in every thread.
-template <typename T> __device__ inline double bq_sum(double v, BqShared<T> &sh) {
-  v = wave_sum(v);
-  __syncthreads();
-  if (threadIdx.x % kWave == 0) sh.wsum[threadIdx.x / kWave] = v;
-  __syncthreads();
-  v = 0.0;
-  for (int w = 0; w < kBqWaves; ++w) v += sh.wsum[w];
-  return v;
-}
-
-template <typename T>
+template <typename T, bool SUM>
 __device__ inline void bq_write(const BatchqArgs<T> &a, uint32_t j, typename Traits<T>::Key key,
-                                int64_t less, int64_t equal, double below, int64_t n, int64_t k,
-                                bool nan) {
-  write_key<T>(a.out + j, key, less, equal, n, 1, nan);
-  if (a.ksum)
-    a.ksum[j] = nan ? __builtin_nan("")
-                    : below + (double)(k - less) * (double)(Traits<T>::unkey(key) + T(0));
+                                int64_t less, int64_t equal, Sum2 below, int64_t n, int64_t k,
+                                int32_t status) {
+  write_key<T>(a.out + j, key, less, equal, n, 1, status);
+  if (SUM)
+    a.ksum[j] = status != ST_OK
+                    ? __builtin_nan("")
+                    : value(sum2(below, product2((double)(k - less), (double)(Traits<T>::unkey(key) + T(0)))));
 }
 
 // An array of at most 512 PER elements.
@@ -239,18 +229,18 @@ __device__ inline void bq_small(const BatchqArgs<T> &a, uint32_t jj, const T *x,
   }
   nan = block_key_range<kBqBlock>(mn, mx, nan, sh.rs);
   if (nan) {  // (uniform)
-    if (tid == 0) bq_write<T>(a, jj, 0, 0, 0, 0.0, n, k, true);
+    if (tid == 0) bq_write<T, SUM>(a, jj, 0, 0, 0, Sum2{}, n, k, ST_NAN);
     return;
   }
   const RegSel<Key> r =
       regs_select<T, kBqBlock, PER>(key, (uint32_t)k, (uint32_t)n, mn, mx, sh.hist, sh.rs);
-  double below = 0.0;
+  Sum2 below = {0.0, 0.0};
   if (SUM) {
 #pragma unroll
-    for (int j = 0; j < PER; ++j) below += key[j] < r.key ? (double)Traits<T>::unkey(key[j]) : 0.0;
-    below = bq_sum<T>(below, sh);
+    for (int j = 0; j < PER; ++j) below.hi += key[j] < r.key ? (double)Traits<T>::unkey(key[j]) : 0.0;
+    below = block_sum2<kBqBlock>(below, sh.sums);
   }
-  if (tid == 0) bq_write<T>(a, jj, r.key, r.less, r.equal, below, n, k, false);
+  if (tid == 0) bq_write<T, SUM>(a, jj, r.key, r.less, r.equal, below, n, k, ST_OK);
 }
 
 // The likely interval from 512 PER samples (runs of kPropRun neighbours at even distances, as
@@ -303,7 +293,7 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
   const bool num = bq_big_sample<T>(n) ? bq_ends<T, kBqSmpB<T>>(sp, n, k, sh, e)
                                        : bq_ends<T, kBqSmpA>(sp, n, k, sh, e);
   if (!num) {  // (uniform, and the same in every part)
-    if (tid == 0 && part == 0) bq_write<T>(a, jj, 0, 0, 0, 0.0, n, k, true);
+    if (tid == 0 && part == 0) bq_write<T, SUM>(a, jj, 0, 0, 0, Sum2{}, n, k, ST_NAN);
     return;
   }
   RowFilter<T> f(e, sh.rows[wv]);
@@ -399,7 +389,7 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
   }
   if (ballot(bad) != 0 && lane == 0) atomicOr(&sh.over, 2u);
   if (rec && held > 0) flush();
-  if (SUM) sum = bq_sum<T>(sum, sh);
+  Sum2 blw = {sum, 0.0};  // (per thread, summed over the workgroup at the end)
   if (lane == 0) {
     sh.held[wv] = held;
     atomicAdd((unsigned long long *)&sh.count[0], (unsigned long long)(f.below - f.ea));
@@ -409,7 +399,6 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
   __syncthreads();
   int64_t lt = (int64_t)sh.count[0], ca = (int64_t)sh.count[1], cb = (int64_t)sh.count[2], inner = 0;
   uint32_t over = sh.over;
-  double blw = sum;
   uint32_t h[4];
   {
     const uint4 q = *reinterpret_cast<const uint4 *>(&sh.hist[4 * tid]);
@@ -420,8 +409,11 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
   }
   if (rec) {
     uint4 *bins = reinterpret_cast<uint4 *>(a.pool + region + room);
+    Sum2 *psum = reinterpret_cast<Sum2 *>(bins + (int64_t)parts * kBqBlock);
     if (parts > 1) {
       bins[(int64_t)part * kBqBlock + tid] = uint4{h[0], h[1], h[2], h[3]};
+      if (SUM) blw = block_sum2<BLOCK>(blw, sh.sums);
+      if (SUM && tid == 0) psum[part] = blw;
       __syncthreads();
     }
     if (tid == 0) {
@@ -429,7 +421,6 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
       if (ca) __hip_atomic_fetch_add(&rec->ea, (uint64_t)ca, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (cb) __hip_atomic_fetch_add(&rec->eb, (uint64_t)cb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (over) __hip_atomic_fetch_or(&rec->over, over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (SUM) __hip_atomic_fetch_add(&rec->sum, blw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint32_t p = atomic_add_release(&rec->arrived, 1u);
       sh.last = p == parts - 1 ? 1u : 0u;
       if (sh.last) fence_acquire();
@@ -458,8 +449,10 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
           }
       }
     }
-    if (SUM)
-      blw = __hip_atomic_load(&rec->sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (SUM && parts > 1) {
+      blw = Sum2{0.0, 0.0};
+      for (uint32_t p = tid; p < parts; p += BLOCK) blw = sum2(blw, psum[p]);
+    }
   } else {
     for (int w = 0; w < kBqWaves; ++w) inner += sh.held[w];
   }
@@ -474,7 +467,6 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
   const int64_t rank = ri < 1 ? 1 : (ri > inner ? inner : ri);
   Key key = e.ka;
   int64_t less = 0, equal = 0;
-  double lsum = 0.0;
   if (inner > 0 && !nan) {
     auto seg_walk = [&](auto &&one) {
       for (uint32_t i = lane; i < (held + kWave - 1) / kWave * kWave; i += kWave)
@@ -499,7 +491,8 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
         }
       }
     };
-    // (SUM: the inside elements below the key, or all of them when the rank is above)
+    // (SUM: the inside elements below the key, all of them when the rank is above, none when below)
+    double lsum = 0.0;
     auto add_inside = [&](T v, bool ok) {
       lsum += ok && (ri > inner || Traits<T>::key(v) < key) ? (double)v : 0.0;
     };
@@ -510,23 +503,22 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
       walk_select<T, BLOCK>(seg_walk, h, rank, e.ia, e.ib, sh.hist, sh.fin, sh.rs, key, less, equal);
       if (SUM) seg_walk(add_inside);
     }
-    if (SUM) lsum = bq_sum<T>(lsum, sh);
+    if (SUM) blw = sum2(blw, Sum2{lsum, 0.0});
   }
+  if (SUM) blw = block_sum2<BLOCK>(blw, sh.sums);
   if (tid == 0) {
-    if (nan) {
-      bq_write<T>(a, jj, 0, 0, 0, 0.0, n, k, true);
-    } else if (ri < 1) {
-      bq_write<T>(a, jj, e.ka, lt, ca, blw, n, k, false);
-    } else if (ri <= inner && equal == 0) {
-      write_selection(a.out + jj, 0, __builtin_nan(""), 0, 0, n, 1, ST_INTERNAL);
-      if (a.ksum) a.ksum[jj] = __builtin_nan("");
-    } else if (ri <= inner) {
-      const double s = blw + (ca ? (double)ca * (double)f.va : 0.0) + lsum;
-      bq_write<T>(a, jj, key, lt + ca + less, equal, s, n, k, false);
+    // at the lower end, inside or at the upper end
+    if (SUM && ri >= 1 && ca) blw = sum2(blw, product2((double)ca, (double)f.va));
+    if (ri < 1) {
+      key = e.ka;
+      less = lt;
+      equal = ca;
     } else {
-      const double s = blw + (ca ? (double)ca * (double)f.va : 0.0) + lsum;
-      bq_write<T>(a, jj, e.kb, lt + ca + inner, cb, s, n, k, false);
+      less = lt + ca + (ri <= inner ? less : inner);
+      key = ri <= inner ? key : e.kb;
+      equal = ri <= inner ? equal : cb;
     }
+    bq_write<T, SUM>(a, jj, key, less, equal, blw, n, k, nan ? ST_NAN : (equal ? ST_OK : ST_INTERNAL));
   }
 }
 
@@ -566,7 +558,7 @@ __global__ __launch_bounds__(kBqBlock, 4) void batchq_kernel(BatchqArgs<T> a) {
         cps_result r = {};
         r.status = ST_BADARG;
         a.out[j] = r;
-        if (a.ksum) a.ksum[j] = __builtin_nan("");
+        if (SUM) a.ksum[j] = __builtin_nan("");
       }
     } else if (n > kBqMaxN) {
       if (tid == 0) bq_redo<T>(a, j);

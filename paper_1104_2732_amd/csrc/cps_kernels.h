@@ -187,10 +187,9 @@ struct BatchqSlot {
 struct BatchqRec {
   uint64_t cursor;           // elements in the array's region of the copy
   uint64_t lt, ea, eb;       // #(x < interval), the two ends' repeated values
-  double sum;                // of the elements below the interval
   int64_t region;            // its region's first element in the pool (-1: none)
   uint32_t arrived, over;    // parts that are done; a part found no room
-  uint64_t pad;
+  uint64_t pad[2];
 };
 template <typename T> struct BatchqArgs {
   const T *const *ptrs;

@@ -408,13 +408,13 @@ __device__ inline void lms_write_nan(cps_result *out, int32_t passes) {
 // (k - #(r < v)) v (Section 6's trimmed sum with the multiplicity of v); one more pass over W.
 template <int BLOCK>
 __device__ inline double lms_ksum(const CPS_GLOBAL double *W, int64_t len, double v, int64_t k,
-                                  int64_t less, double below, double *wred) {
+                                  int64_t less, double below, Sum2 *red) {
   double part = 0.0;
   for_each8<BLOCK>(W, len, [&](double r) {
     if (r < v) part += r;
   });
-  const double s = block_sum_fixed<BLOCK>(part, wred);
-  return below + s + (double)(k - less) * v;
+  const Sum2 s = block_sum2<BLOCK>(Sum2{part, 0.0}, red);
+  return value(sum2(sum2(Sum2{below, 0.0}, s), product2((double)(k - less), v)));
 }
 
 // One workgroup per candidate: the segments' counts and the bracket's test; where it holds, the
@@ -438,6 +438,7 @@ __global__ __launch_bounds__(kLmsSelBlock, 8) void lms_select_kernel(
   __shared__ uint64_t fin[kWalkFinal];
   __shared__ RegSelShared<BLOCK> sh;
   __shared__ double wred[BLOCK / kWave];
+  __shared__ Sum2 sums[BLOCK / kWave];
   const int64_t per = (m + 7) / 8, c = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   if (c >= m) return;
   const int tid = threadIdx.x;
@@ -538,9 +539,9 @@ __global__ __launch_bounds__(kLmsSelBlock, 8) void lms_select_kernel(
     double sb = 0.0, part = 0.0;
     for (int64_t s = tid; s < nseg; s += BLOCK) sb += psum[s * m + c];
     walk([&](double r, bool ok) { part += ok && r < v ? r : 0.0; });
-    const double under = block_sum_fixed<BLOCK>(sb, wred);
-    const double mid = block_sum_fixed<BLOCK>(part, wred);
-    if (tid == 0) ksum[c] = under + mid + (double)(k - below - less) * v;
+    const Sum2 under = block_sum2<BLOCK>(Sum2{sb, 0.0}, sums);
+    const Sum2 mid = block_sum2<BLOCK>(Sum2{part, 0.0}, sums);
+    if (tid == 0) ksum[c] = value(sum2(sum2(under, mid), product2((double)(k - below - less), v)));
   }
 }
 
@@ -553,7 +554,7 @@ __global__ __launch_bounds__(kLmsGatherBlock) void lms_full_select_kernel(
   __shared__ uint32_t hist[kHistMaxBins];
   __shared__ double buf[kLmsSelCap];
   __shared__ WgSelLds sh;
-  __shared__ double wred[kLmsGatherBlock / kWave];
+  __shared__ Sum2 sums[kLmsGatherBlock / kWave];
   const int64_t c = blockIdx.x;
   const int tid = threadIdx.x;
   if (full[c] == 0) return;  // (uniform)
@@ -588,7 +589,7 @@ __global__ __launch_bounds__(kLmsGatherBlock) void lms_full_select_kernel(
   if (tid == 0) lms_write_result(out + c, r.key, r.less, r.equal, n, 3 + r.passes);
   if (ksum) {  // (uniform)
     const double t = lms_ksum<kLmsGatherBlock>(Rc, n, Traits<double>::unkey(r.key), k, r.less,
-                                               0.0, wred);
+                                               0.0, sums);
     if (tid == 0) ksum[c] = t;
   }
 }

@@ -52,12 +52,12 @@ __global__ __launch_bounds__(BLOCK) void quick_small_kernel(const T *__restrict_
   }
   nan = block_key_range<BLOCK>(mn, mx, nan, sh);
   if (nan) {  // (uniform)
-    if (tid == 0) write_key<T>(out, 0, 0, 0, n, 1, true);
+    if (tid == 0) write_key<T>(out, 0, 0, 0, n, 1, ST_NAN);
     return;
   }
   const RegSel<Key> r =
       regs_select<T, BLOCK, PER>(key, (uint32_t)k, (uint32_t)n, mn, mx, hist, sh);
-  if (tid == 0) write_key<T>(out, r.key, r.less, r.equal, n, 1, false);
+  if (tid == 0) write_key<T>(out, r.key, r.less, r.equal, n, 1, ST_OK);
 }
 
 // ------------------------------------------------------------------ the filter

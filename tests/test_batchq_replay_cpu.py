@@ -63,7 +63,8 @@ def check(esize, pool, addrs, sizes, ks, head, slots, items):
         if region < 0:
             continue
         assert shared[index] and region % 64 == 0 and region >= end
-        end = region + -(-(sizes[index] // 16) // 64) * 64 + parts * 8192 // esize
+        end = (region + -(-(sizes[index] // 16) // 64) * 64 + parts * 8192 // esize +
+               -(-parts * 16 // esize // 64) * 64)
         assert end <= pool
     # items: consecutive, each slot's parts in turn
     assert [q for q, *_ in items] == list(range(head["items"]))
