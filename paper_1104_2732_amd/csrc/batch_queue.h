@@ -90,12 +90,15 @@ CPS_HD inline constexpr int64_t bq_small_max(uint32_t esize) { return esize == 4
 CPS_HD inline constexpr int64_t bq_share(uint32_t esize) { return (int64_t)1 << (esize == 4 ? 18 : 16); }
 CPS_HD inline bool bq_shared(int64_t n, uint32_t esize) { return n >= bq_share(esize) && n <= kBqMaxN; }
 // A shared array's region of the pool: room for a sixteenth of its elements (the interval holds
-// 3.6 % of them, of float64 4.1 %, give or take 5 % of that), then the key bins of each part, then
-// each part's sum of the elements below the interval, in two doubles.  Arrays that find no region are left to the general kernel unread.
+// 3.6 % of them, of float64 4.1 %, give or take 5 % of that), whose last places take each part's sum
+// of the elements below the interval (two doubles), then the key bins of each part.  (A batch of
+// 2^30 elements in parts of 2^20 fills the default pool to the last place.)  Arrays that find no region are left to the general kernel unread.
 CPS_HD inline int64_t bq_room(int64_t n) { return (n / 16 + 63) / 64 * 64; }
+CPS_HD inline int64_t bq_copy_room(int64_t n, uint32_t parts, uint32_t esize) {
+  return bq_room(n) - (int64_t)parts * (int64_t)(2 * sizeof(double) / esize);
+}
 CPS_HD inline int64_t bq_region(int64_t n, uint32_t parts, uint32_t esize) {
-  return bq_room(n) + (int64_t)parts * (int64_t)(kBqBins * sizeof(uint32_t) / esize) +
-         ((int64_t)parts * (int64_t)(2 * sizeof(double) / esize) + 63) / 64 * 64;
+  return bq_room(n) + (int64_t)parts * (int64_t)(kBqBins * sizeof(uint32_t) / esize);
 }
 
 // Eight size classes per power of two; the limit of sharing is a class limit, so the shared

@@ -297,7 +297,7 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
     return;
   }
   RowFilter<T> f(e, sh.rows[wv]);
-  const int64_t region = rec ? rec->region : 0, room = bq_room(n);
+  const int64_t region = rec ? rec->region : 0, room = bq_copy_room(n, parts, sizeof(T));
   CPS_GLOBAL T *z = (CPS_GLOBAL T *)(a.pool + region);
   if (tid < 3) sh.count[tid] = 0ull;
   if (tid == 0) sh.over = 0u;  // (1: no room; 2: NaN)
@@ -408,8 +408,8 @@ __device__ inline void bq_large(const BatchqArgs<T> &a, uint32_t jj, const T *x,
     h[3] = q.w;
   }
   if (rec) {
-    uint4 *bins = reinterpret_cast<uint4 *>(a.pool + region + room);
-    Sum2 *psum = reinterpret_cast<Sum2 *>(bins + (int64_t)parts * kBqBlock);
+    uint4 *bins = reinterpret_cast<uint4 *>(a.pool + region + bq_room(n));
+    Sum2 *psum = reinterpret_cast<Sum2 *>(a.pool + region + room);
     if (parts > 1) {
       bins[(int64_t)part * kBqBlock + tid] = uint4{h[0], h[1], h[2], h[3]};
       if (SUM) blw = block_sum2<BLOCK>(blw, sh.sums);

@@ -63,8 +63,7 @@ def check(esize, pool, addrs, sizes, ks, head, slots, items):
         if region < 0:
             continue
         assert shared[index] and region % 64 == 0 and region >= end
-        end = (region + -(-(sizes[index] // 16) // 64) * 64 + parts * 8192 // esize +
-               -(-parts * 16 // esize // 64) * 64)
+        end = region + -(-(sizes[index] // 16) // 64) * 64 + parts * 8192 // esize
         assert end <= pool
     # items: consecutive, each slot's parts in turn
     assert [q for q, *_ in items] == list(range(head["items"]))
@@ -121,6 +120,16 @@ def test_every_array_once(replay, tmp_path, esize, count, top, pool):
     elif pool == 1 << 33:
         # every array but those of about 2^30 elements and more has a region
         assert listed.sum() == 2 + sum(n > 1 << 29 and n <= MAX_N for n in sizes)
+
+
+@pytest.mark.parametrize("count,n", [(1024, 1 << 20), (512, 1 << 21), (256, 1 << 22), (64, 1 << 24)])
+def test_float64_batch_that_fills_the_default_pool(replay, tmp_path, count, n):
+    """2^30 float64 elements (1024 candidates' squares over 2^20 rows among them): every array of
+    equal size has a region of the default pool, 256 workgroups' workspaces."""
+    addrs, sizes, ks = [BASE + 4096 * i for i in range(count)], [n] * count, [n // 2] * count
+    pool = 256 * ((1 << 18) + 4096)
+    head, slots, items = run(replay, tmp_path, 8, 512, pool, addrs, sizes, ks)
+    assert check(8, pool, addrs, sizes, ks, head, slots, items).sum() == 0
 
 
 @pytest.mark.parametrize("esize", [4, 8])
