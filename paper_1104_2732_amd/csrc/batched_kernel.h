@@ -958,10 +958,13 @@ __device__ void select_one(const T *x, int64_t n, int64_t k, cps_result *out, do
 template <typename T, int BLOCK, int U, bool LIST>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_num_vgpr(128)))
 void batched_select_kernel(BatchArgs<T> a) {
+  // Nothing was left to this kernel, as nearly always (the queue is untouched).  The hint keeps this
+  // way out at the kernel's beginning: a jump to its far end cost 1.3 of 29.6 us for a batch of 300
+  // x 4000 float64 elements.
+  if (LIST && __builtin_expect(*a.list_count == 0u, 1)) return;
   __shared__ BShared<T, BLOCK> sh;
   const int tid = threadIdx.x;
   const int64_t count = LIST ? (int64_t)*a.list_count : a.count;
-  if (LIST && count == 0) return;  // (nothing was left to this kernel; the queue is untouched)
   if (tid == 0) sh.cfg = a.cfg;  // (read after the barriers below)
   // Largest first: every workgroup sorts (size, index) in LDS by itself.
   const bool sorted = !LIST && count <= kBatchSortMax;

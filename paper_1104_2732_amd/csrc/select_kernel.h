@@ -25,8 +25,8 @@
 //               ordered keys).
 // Between passes the grid synchronises through two-level arrival counters; the last
 // workgroup to arrive reduces the per-workgroup partials in a fixed order and advances
-// the cutting-plane state (cp_state.h), so no pass needs the host.  The kernel is
-// launched cooperatively, which guarantees that every workgroup is resident.
+// the cutting-plane state (cp_state.h), so no pass needs the host.  The grid never exceeds
+// what fits, so all workgroups are resident (a cooperative launch guarantees it; cps_options).
 //
 // The kernel has two instances, each in a translation unit of its own (select.hip,
 // select_quick.hip): with both in one, the functions that they share lose what the compiler knows
