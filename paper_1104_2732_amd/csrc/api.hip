@@ -53,6 +53,7 @@ namespace {
 // gather buffer.
 struct SelectLayout {
   size_t st, sync, gh, qsync, qhist, qrec, qslot, qkept, qcnt, sd, si, z0, z1, zf, sm, zq, total;
+  size_t quick_bytes, slot_bytes;  // of these, the one-read selection's counters and gather slots
   int64_t slot_stride, seg_R, zcap, smp_n;
 };
 
@@ -84,6 +85,7 @@ SelectLayout select_layout(int64_t seg_R, int grid, int64_t zcap, int gmax, size
     L.qcnt = off;
     off = align_up(off + (size_t)gmax * sizeof(uint32_t), 256);
   }
+  L.quick_bytes = off - L.qsync;
   L.sd = off;
   off = align_up(off + 8 * (size_t)gmax * sizeof(double), 256);
   L.si = off;
@@ -102,6 +104,7 @@ SelectLayout select_layout(int64_t seg_R, int grid, int64_t zcap, int gmax, size
   off = align_up(off + (size_t)smp_n * esize, 256);
   L.zq = off;
   if (slots > 0) off = align_up(off + (size_t)slots * cps::kQuickGather * esize, 256);
+  L.slot_bytes = off - L.zq;
   L.total = off;
   return L;
 }
@@ -118,14 +121,25 @@ int64_t spec_sample_elems(int64_t n, size_t esize, int64_t spec_min_n) {
 
 // Grow a workspace buffer to at least `bytes`.  The synchronisation words at the start of
 // every layout must be zero on first use, so fresh memory is cleared synchronously.
-int ensure_buffer(void *&buf, size_t &have, size_t bytes, hipStream_t stream);
+int ensure_buffer(void *&buf, size_t &have, size_t bytes, hipStream_t stream, size_t more = 0);
 
-int ensure_workspace(cps_handle *h, size_t bytes, hipStream_t stream) {
-  return ensure_buffer(h->ws, h->ws_bytes, bytes, stream);
+// The single-array workspace.  A call needs the gather slots only if it takes the one-read selection;
+// what is allocated has room for those of any call whose other parts fit it (a call's slots are at
+// most half of its split buffers), so a call leaves enough for the same and smaller ones of any
+// kind, under capture too.
+int ensure_workspace(cps_handle *h, const SelectLayout &L, bool slots, hipStream_t stream) {
+  const size_t base = L.total - L.slot_bytes - L.quick_bytes, need = L.total - (slots ? 0 : L.slot_bytes);
+  if (need <= h->ws_bytes) return CPS_OK;
+  const int per_cu = h->max_blocks_f32 > h->max_blocks_f64 ? h->max_blocks_f32 : h->max_blocks_f64;
+  const size_t most = (size_t)h->cu_count * per_cu * cps::kQuickGather * sizeof(double);
+  const size_t half = align_up(base + base / 8, 1 << 20) / 2;
+  const size_t room = L.quick_bytes + (half < most ? half : most);
+  return ensure_buffer(h->ws, h->ws_bytes, base, stream, room > need - base ? room : need - base);
 }
 
-int ensure_buffer(void *&buf, size_t &have, size_t bytes, hipStream_t stream) {
-  if (bytes <= have) return CPS_OK;
+// more: bytes beyond `bytes` and its slack to allocate, where it has to be.
+int ensure_buffer(void *&buf, size_t &have, size_t bytes, hipStream_t stream, size_t more) {
+  if (bytes + more <= have) return CPS_OK;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (stream != nullptr) {
     hipError_t e = hipStreamIsCapturing(stream, &cs);
@@ -139,7 +153,7 @@ int ensure_buffer(void *&buf, size_t &have, size_t bytes, hipStream_t stream) {
     buf = nullptr;
     have = 0;
   }
-  size_t want = align_up(bytes + bytes / 8, 1 << 20);
+  const size_t want = align_up(align_up(bytes + bytes / 8, 1 << 20) + more, 1 << 20);
   e = hipMalloc(&buf, want);
   if (e != hipSuccess) {
     (void)hipGetLastError();  // (not the next launch's)
@@ -293,8 +307,7 @@ bool default_method(const cps_options *opt) {
 constexpr size_t kQuickCopyBytes = (size_t)1 << 26;
 
 // The one-read selection's workgroups for n elements (none: one workgroup's registers hold them, or
-// its 32-bit counts do not).  Every layout for n has their slots, whatever the call's options, so
-// that what one call of n leaves serves any other.
+// its 32-bit counts do not).
 template <typename T> int64_t quick_slots(int64_t n, int gmax) {
   if (n <= cps::quick_small_max<T>() || n > cps::kQuickMaxN) return 0;
   const int64_t tile = (int64_t)cps::kSelectBlock * cps::kSelectUnroll * (16 / (int64_t)sizeof(T));
@@ -322,7 +335,7 @@ int run_select(cps_handle *h, const T *x, int64_t n, int64_t k, const cps_option
   const bool quick = plain && k > 1 && k < n && r.grid <= slots && r.grid <= 1024;
   const SelectLayout L = select_layout(r.seg_R, r.grid, r.cfg.zcap, gmax, sizeof(T),
                                        spec_sample_elems(n, sizeof(T), r.cfg.spec_min_n), slots);
-  rc = ensure_workspace(h, L.total, stream);
+  rc = ensure_workspace(h, L, quick, stream);
   if (plain && n <= cps::quick_small_max<T>() && rc != CPS_EHIP) {
     // (it needs no workspace; what it leaves serves a later call of n with options or a trace,
     // which may be under capture)
@@ -1036,7 +1049,7 @@ int cps_reserve(cps_handle *h, int64_t n, int dtype) {
       select_layout(r.seg_R, r.grid, r.cfg.zcap, gmax, dtype_size(dtype),
                     spec_sample_elems(n, dtype_size(dtype), r.cfg.spec_min_n),
                     dtype == CPS_F32 ? quick_slots<float>(n, gmax) : quick_slots<double>(n, gmax));
-  return ensure_workspace(h, L.total, nullptr);
+  return ensure_workspace(h, L, L.slot_bytes > 0, nullptr);
 }
 
 int select_kth_ex(cps_handle *h, const void *x, int64_t n, int64_t k, int dtype,
